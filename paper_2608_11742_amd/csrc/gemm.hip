@@ -3,8 +3,9 @@
 //   swiglu : f = silu(a Wg^T) * (a Wu^T)     (gate/up projection)
 //   qkv    : q, k, v = a Wqkv^T, rotary embedding on q and k, scattered to
 //            head-major Q/K and transposed V
-// 256x256 output tiles, 8 waves of 64x128, bf16 (or fp32) MFMA, fp32 accumulate;
-// fewer rows take the smaller tile configurations below.
+// 256x256 output tiles, 8 waves of 64x128, bf16 MFMA, fp32 accumulate; fewer
+// rows take the smaller tile configurations below.  fp32 models take
+// gemm_f32_kernel.
 //
 // Few rows (a 512-row forward has 32 output tiles in the O and down
 // projections for 256 CUs): the K range is split into parts, every part
@@ -357,7 +358,8 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (Elem<T>::bytes == 2) {
+    static_assert(Elem<T>::bytes == 2, "fp32 takes gemm_f32_kernel");
+    {
       const int r0 = m0 + wm * TM::kWTM;
       if (which < 2) {
         // Q, K: stage the wave's 64 x 128 bf16 tile in its own region of the
@@ -447,25 +449,6 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
           }
         }
       }
-    } else {
-      // fp32 activations: direct element stores
-#pragma unroll
-      for (int m = 0; m < TM::kFM; ++m)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = row_base + m * 16 + i;
-          if (row >= M) continue;
-          const int b = row / o.seq, sp = row % o.seq;
-#pragma unroll
-          for (int n = 0; n < TM::kFN; ++n) {
-            const int cin = cin0 + n * 16 + lc;
-            const int h = cin / hd, dim = cin % hd;
-            T* dst = which == 2 ? reinterpret_cast<T*>(o.vt) + (size_t(b * o.H + h) * hd + dim) * o.vt_ld + sp
-                                : reinterpret_cast<T*>(which == 0 ? o.q : o.k) + (size_t(b * o.H + h) * o.seq + sp) * hd +
-                                      dim;
-            store_f(dst, acc[m][n][i]);
-          }
-        }
     }
   }
 }
@@ -512,6 +495,171 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_swiglu_pe
   }
 }
 
+// ---------------------------------------------------------------- fp32 projections
+
+// fp32 tile: 64 x 64, 4 waves of 16 x 64, four workgroups to a CU.  The fp32
+// matrix instructions run at a sixteenth of the bf16 rate, so a projection is
+// bound by them as soon as every SIMD has a wave, and by idle SIMDs before
+// that: this tile is small enough that a few hundred rows spread over all CUs,
+// while its LDS and L2 traffic stays far below their rates.  Measured against
+// 256 x 256 tiles of 8 waves: 603 x 8192 x 1024 124 -> 89 us (114 TFLOP/s),
+// 512 x 2048 x 256 37 -> 9 us, and a d 4096 layer of 2048 rows 7.7 -> 7.1 ms;
+// 128 x 128 tiles were within 3% at 2048 rows and up to 7% slower below.
+// A row's columns lie in one wave, blocks transposed (TileMma TRANS), so every
+// epilogue works on 4 consecutive columns of a row in registers and stores 16
+// bytes without LDS.
+struct F32Cfg {
+  static constexpr int BM = 64, BN = 64, kThreads = 256, kMinBlocks = 4;
+  using TM = TileMma<float, BM, BN, 4, 1, true>;
+};
+
+// x (or a part) of the fp32 projection A B^T with the epilogue applied in
+// registers.  Tile columns n and n + BN / 2 belong together: the gate and up
+// rows of one output, or the two halves of a rotary pair (QKV); the residual
+// projection and its split-K parts take plain columns.
+template <int EPI, int HD>
+__global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32_kernel(
+    const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int M, int N, int K, int tiles_m,
+    int tiles_n, EpiParams ep) {
+  using Cfg = F32Cfg;
+  using TM = Cfg::TM;
+  constexpr int kHalf = Cfg::BN / 2, kHN = TM::kFN / 2;
+  constexpr bool kSplit = EPI == EPI_PART || EPI == EPI_PART_GU;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[TM::kSmem];
+  int tm, tn, part = 0;
+  if constexpr (kSplit)
+    map_split_tile(tiles_m, tiles_n, gridDim.y, tm, tn, part);
+  else
+    map_tile(blockIdx.x, gridDim.x, tiles_m, tiles_n, kGroupM, tm, tn);
+  const int m0 = tm * Cfg::BM;
+  const uint32_t a_row_bytes = uint32_t(lda) * 4, b_row_bytes = uint32_t(ldb) * 4;
+  int st0 = 0, nst = K / (2 * TM::kKPerStage);
+  if constexpr (kSplit) {
+    const int all = nst;
+    st0 = part * all / int(gridDim.y);
+    nst = (part + 1) * all / int(gridDim.y) - st0;
+  }
+  const uint32_t k_bytes = uint32_t(st0) * TM::kRowBytes;
+  auto a_off = [&](int r) -> uint32_t { return uint32_t(min(m0 + r, M - 1)) * a_row_bytes + k_bytes; };
+  auto b_off = [&](int r) -> uint32_t {
+    int row;
+    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_PART_GU) {
+      const int j = min(tn * kHalf + r % kHalf, ep.F - 1);
+      row = r < kHalf ? j : ep.F + j;
+    } else if constexpr (EPI == EPI_QKV) {
+      // rotary pair p: dims p % (HD / 2) and that + HD / 2 of head column p / (HD / 2)
+      const int p = tn * kHalf + r % kHalf;
+      row = min((p / (HD / 2)) * HD + p % (HD / 2) + (r < kHalf ? 0 : HD / 2), N - 1);
+    } else {
+      row = min(tn * Cfg::BN + r, N - 1);
+    }
+    return uint32_t(row) * b_row_bytes + k_bytes;
+  };
+  f32x4 acc[TM::kFM][TM::kFN];
+  TM::run(smem, reinterpret_cast<const uint8_t*>(A), reinterpret_cast<const uint8_t*>(B), a_off, b_off, 2 * nst,
+          acc);
+
+  // lane l: row 16 m + l % 16 of the wave tile, columns 16 n + 4 (l / 16) + 0 .. 3
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = m0 + wave * TM::kWTM + (lane & 15), c4 = 4 * (lane >> 4);
+  if constexpr (EPI == EPI_PART) {
+    float* P = ep.part + size_t(part) * M * ep.np;
+#pragma unroll
+    for (int m = 0; m < TM::kFM; ++m) {
+      const int row = r0 + 16 * m;
+      if (row >= M) continue;
+#pragma unroll
+      for (int n = 0; n < TM::kFN; ++n) {
+        const int col = tn * Cfg::BN + 16 * n + c4;
+        if (col < ep.np) *reinterpret_cast<f32x4*>(P + size_t(row) * ep.np + col) = acc[m][n];
+      }
+    }
+  } else if constexpr (EPI == EPI_PART_GU) {
+    // partial columns in the layout splitk_swiglu_kernel reads
+    float* P = ep.part + size_t(part) * M * ep.np;
+#pragma unroll
+    for (int m = 0; m < TM::kFM; ++m) {
+      const int row = r0 + 16 * m;
+      if (row >= M) continue;
+#pragma unroll
+      for (int n = 0; n < kHN; ++n) {
+        const int j = tn * kHalf + 16 * n + c4;
+        if (j >= ep.F) continue;
+        float* dst = P + size_t(row) * ep.np + (j >> 7) * 256 + ((j & 127) >> 6) * 128 + (j & 63);
+        *reinterpret_cast<f32x4*>(dst) = acc[m][n];
+        *reinterpret_cast<f32x4*>(dst + 64) = acc[m][n + kHN];
+      }
+    }
+  } else if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+    for (int m = 0; m < TM::kFM; ++m) {
+      const int row = r0 + 16 * m;
+      if (row >= M) continue;
+      float* xr = ep.x + size_t(row) * ep.ldx;
+#pragma unroll
+      for (int n = 0; n < TM::kFN; ++n) {
+        const int col = tn * Cfg::BN + 16 * n + c4;
+        if (col < N) *reinterpret_cast<f32x4*>(xr + col) = *reinterpret_cast<const f32x4*>(xr + col) + acc[m][n];
+      }
+    }
+  } else if constexpr (EPI == EPI_SWIGLU) {
+    float* out = static_cast<float*>(ep.out);
+    const bool vec = (ep.F % 4) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+#pragma unroll
+    for (int m = 0; m < TM::kFM; ++m) {
+      const int row = r0 + 16 * m;
+      if (row >= M) continue;
+#pragma unroll
+      for (int n = 0; n < kHN; ++n) {
+        const int j = tn * kHalf + 16 * n + c4;
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = silu_fast(acc[m][n][i]) * acc[m][n + kHN][i];
+        float* dst = out + size_t(row) * ep.F + j;
+        if (vec && j + 3 < ep.F) {
+          *reinterpret_cast<f32x4*>(dst) = v;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (j + i < ep.F) dst[i] = v[i];
+        }
+      }
+    }
+  } else {   // EPI_QKV
+    const QkvOut& o = ep.qkv;
+    constexpr int half = HD / 2;
+#pragma unroll
+    for (int m = 0; m < TM::kFM; ++m) {
+      const int row = r0 + 16 * m;
+      if (row >= M) continue;
+      const int b = row / o.seq, sp = row - b * o.seq;
+      const float2* rope = o.rope + size_t(qkv_pos(o, row)) * half;
+#pragma unroll
+      for (int n = 0; n < kHN; ++n) {
+        const int p = tn * kHalf + 16 * n + c4, hc = p / half, dim = p % half;
+        if (p >= N / 2) continue;
+        const int which = hc / o.H, h = hc - which * o.H;
+        const f32x4 x1 = acc[m][n], x2 = acc[m][n + kHN];
+        if (which < 2) {
+          const float4* cs4 = reinterpret_cast<const float4*>(rope + dim);
+          const float4 c01 = cs4[0], c23 = cs4[1];   // (cos, sin) of dims dim .. dim + 3
+          const f32x4 cs = f32x4{c01.x, c01.z, c23.x, c23.z}, sn = f32x4{c01.y, c01.w, c23.y, c23.w};
+          float* dst = static_cast<float*>(which == 0 ? o.q : o.k) + (size_t(b * o.H + h) * o.seq + sp) * HD + dim;
+          *reinterpret_cast<f32x4*>(dst) = x1 * cs - x2 * sn;
+          *reinterpret_cast<f32x4*>(dst + half) = x1 * sn + x2 * cs;
+        } else {
+          float* dst = static_cast<float*>(o.vt) + (size_t(b * o.H + h) * HD + dim) * o.vt_ld + sp;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            dst[size_t(i) * o.vt_ld] = x1[i];
+            dst[size_t(i + half) * o.vt_ld] = x2[i];
+          }
+        }
+      }
+    }
+  }
+}
+
 // compute units of the current device (cached per device)
 int device_cus() {
   static int cus[64] = {0};
@@ -545,6 +693,41 @@ hipError_t launch(int bm, const void* A, int lda, const void* B, int ldb, int M,
   if (bm == Small::BM) return launch_cfg<T, EPI, HD, Small>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
   if (bm == Quad::BM) return launch_cfg<T, EPI, HD, Quad>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
   return launch_cfg<T, EPI, HD, Big>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
+}
+
+// K parts of an fp32 projection: the smallest estimated time in us over 1, 2,
+// 4, 8 or 16 parts of at least 4 stages.  A 64 x 64 tile takes 0.44 us per K
+// stage at the fp32 MFMA rate of its CU, shared by the workgroups the CU
+// holds; one alone reaches half of that (1.8 instead of 1, measured 0.8 us a
+// stage).  The parts are written and read once at about 4 TB/s; their sum is
+// part of the following norm (residual projections) or a launch of its own.
+int f32_splits(int kind, int M, int N, int K) {
+  const int tiles = cdiv(M, F32Cfg::BM) * cdiv(N, F32Cfg::BN), stages = K / 32;
+  int best = 1;
+  double best_us = 0.0;
+  for (int p = 1; p <= 16 && (p == 1 || stages / p >= 4); p *= 2) {
+    const double per_cu = std::max(1.8, double(cdiv(tiles * p, 256)));
+    double us = 0.44 * cdiv(stages, p) * per_cu;
+    if (p > 1) us += (kind == GEMM_KIND_RESID ? 2.0 : 5.0) + 2.0 * p * M * N * 4.0 / 4e6;
+    if (p == 1 || us < best_us) {
+      best = p;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+template <int EPI, int HD = 0>
+hipError_t launch_f32(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const EpiParams& ep,
+                      hipStream_t s, int splits = 1) {
+  constexpr int kStageK = 2 * F32Cfg::TM::kKPerStage;
+  if (K <= 0 || K % kStageK || splits < 1 || splits > K / kStageK) return hipErrorInvalidValue;
+  // gate/up tiles hold BN / 2 outputs of each kind: N = 2 F columns in all
+  const int tiles_m = cdiv(M, F32Cfg::BM), tiles_n = cdiv(N, F32Cfg::BN);
+  hipLaunchKernelGGL((gemm_f32_kernel<EPI, HD>), dim3(tiles_m * tiles_n, splits), dim3(F32Cfg::kThreads), 0, s,
+                     static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, M, N, K, tiles_m, tiles_n,
+                     ep);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- split-K reductions
@@ -732,13 +915,14 @@ hipError_t splitk_add(const SplitK& sk, int M, int N, float* X, int ldx, hipStre
 }
 
 int gemm_splits(int kind, int M, int N, int K, int dtype) {
+  if (!dtype) return f32_splits(kind, M, N, K);
   // workgroups that fill the 256 CUs: one Big, Mid or Quad workgroup per CU, two Small ones
   const int bm = tile_rows(kind, M, N, K);
   const int tiles_n = kind == GEMM_KIND_GATEUP ? cdiv(N / 2, 128)
                       : kind == GEMM_KIND_QKV && qkv_mid_parts(M, N) ? N / Mid::BN
                                                                        : cdiv(N, kBN);
   const int tiles = cdiv(M, bm) * tiles_n, full = bm == Small::BM ? 512 : 256;
-  const int stages = K / (dtype ? 64 : 32);   // 128-byte K stages
+  const int stages = K / 64;   // 128-byte K stages
   if (tiles >= full * 5 / 8 || stages < 2) return 1;
   const int parts = std::max(1, std::min(full / tiles, stages / 4));
   // a multiple of 8 or a power of two, so that map_split_tile gives each
@@ -765,12 +949,12 @@ hipError_t gemm_resid(int dtype, const void* A, int lda, const void* B, int ldb,
     ep.part = sk->part;
     ep.np = tn * kBN;
     hipError_t e = dtype ? launch<bf16_t, EPI_PART>(bm, A, lda, B, ldb, M, N, K, tn, ep, s, sk->splits)
-                         : launch<float, EPI_PART>(bm, A, lda, B, ldb, M, N, K, tn, ep, s, sk->splits);
+                         : launch_f32<EPI_PART>(A, lda, B, ldb, M, N, K, ep, s, sk->splits);
     if (e != hipSuccess || sk->defer) return e;
     return splitk_add(*sk, M, N, X, ldx, s);
   }
   return dtype ? launch<bf16_t, EPI_RESID>(bm, A, lda, B, ldb, M, N, K, tn, ep, s)
-               : launch<float, EPI_RESID>(bm, A, lda, B, ldb, M, N, K, tn, ep, s);
+               : launch_f32<EPI_RESID>(A, lda, B, ldb, M, N, K, ep, s);
 }
 
 hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M, int F, int K, void* out,
@@ -778,11 +962,11 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
   EpiParams ep{};
   ep.out = out;
   ep.F = F;
+  if (!dtype && !(sk && sk->splits > 1)) return launch_f32<EPI_SWIGLU>(A, lda, Wgu, K, M, 2 * F, K, ep, s);
   const int bm = tile_rows(GEMM_KIND_GATEUP, M, 2 * F, K);
   if (!(sk && sk->splits > 1) && M > 256 && M <= 512 && bm == Big::BM) {
     const int tm = cdiv(F, Mid::BN / 2);
-    return dtype ? launch_cfg<bf16_t, EPI_SWIGLU, 0, Mid>(A, lda, Wgu, K, M, 2 * F, K, tm, ep, s, 1)
-                 : launch_cfg<float, EPI_SWIGLU, 0, Mid>(A, lda, Wgu, K, M, 2 * F, K, tm, ep, s, 1);
+    return launch_cfg<bf16_t, EPI_SWIGLU, 0, Mid>(A, lda, Wgu, K, M, 2 * F, K, tm, ep, s, 1);
   }
   const int tn = cdiv(F, 128);
   if (sk && sk->splits > 1) {
@@ -790,7 +974,7 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
     ep.part = sk->part;
     ep.np = tn * kBN;
     hipError_t e = dtype ? launch<bf16_t, EPI_PART_GU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s, sk->splits)
-                         : launch<float, EPI_PART_GU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s, sk->splits);
+                         : launch_f32<EPI_PART_GU>(A, lda, Wgu, K, M, 2 * F, K, ep, s, sk->splits);
     if (e != hipSuccess) return e;
     const dim3 g(cdiv(M * (F / 4), kRedThreads));
     if (dtype)
@@ -803,21 +987,15 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
   }
   if (bm == Big::BM) {
     // 256 x 256 tiles, one persistent workgroup per CU
-    const int stage_k = dtype ? 2 * TileMma<bf16_t, Big::BM, Big::BN, Big::WM, Big::WN>::kKPerStage
-                              : 2 * TileMma<float, Big::BM, Big::BN, Big::WM, Big::WN>::kKPerStage;
-    if (K <= 0 || K % stage_k) return hipErrorInvalidValue;
+    constexpr int kStageK = 2 * TileMma<bf16_t, Big::BM, Big::BN, Big::WM, Big::WN>::kKPerStage;
+    if (K <= 0 || K % kStageK) return hipErrorInvalidValue;
     const int tiles_m = cdiv(M, Big::BM), tiles = tiles_m * tn;
     const int grid = std::min(tiles, device_cus());
-    if (dtype)
-      hipLaunchKernelGGL((gemm_swiglu_persist_kernel<bf16_t, Big>), dim3(grid), dim3(Big::kThreads), 0, s,
-                         static_cast<const bf16_t*>(A), lda, static_cast<const bf16_t*>(Wgu), M, K, tiles_m, tn, ep);
-    else
-      hipLaunchKernelGGL((gemm_swiglu_persist_kernel<float, Big>), dim3(grid), dim3(Big::kThreads), 0, s,
-                         static_cast<const float*>(A), lda, static_cast<const float*>(Wgu), M, K, tiles_m, tn, ep);
+    hipLaunchKernelGGL((gemm_swiglu_persist_kernel<bf16_t, Big>), dim3(grid), dim3(Big::kThreads), 0, s,
+                       static_cast<const bf16_t*>(A), lda, static_cast<const bf16_t*>(Wgu), M, K, tiles_m, tn, ep);
     return hipGetLastError();
   }
-  return dtype ? launch<bf16_t, EPI_SWIGLU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s)
-               : launch<float, EPI_SWIGLU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s);
+  return launch<bf16_t, EPI_SWIGLU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s);
 }
 
 namespace {
@@ -831,10 +1009,13 @@ hipError_t qkv_split(const void* A, int lda, const void* Wqkv, int M, int K, con
   const int N = 3 * o.d, tn = cdiv(N, kBN);
   ep.part = sk.part;
   ep.np = tn * kBN;   // the partial layout does not depend on the tiling
-  hipError_t e = qkv_mid_parts(M, N)
-                     ? launch_cfg<T, EPI_PART, 0, Mid>(A, lda, Wqkv, K, M, N, K, N / Mid::BN, ep, s, sk.splits)
-                     : launch<T, EPI_PART>(tile_rows(GEMM_KIND_QKV, M, N, K), A, lda, Wqkv, K, M, N, K, tn, ep, s,
-                                           sk.splits);
+  hipError_t e;
+  if constexpr (std::is_same_v<T, float>)
+    e = launch_f32<EPI_PART>(A, lda, Wqkv, K, M, N, K, ep, s, sk.splits);
+  else if (qkv_mid_parts(M, N))
+    e = launch_cfg<T, EPI_PART, 0, Mid>(A, lda, Wqkv, K, M, N, K, N / Mid::BN, ep, s, sk.splits);
+  else
+    e = launch<T, EPI_PART>(tile_rows(GEMM_KIND_QKV, M, N, K), A, lda, Wqkv, K, M, N, K, tn, ep, s, sk.splits);
   if (e != hipSuccess) return e;
   const int n_qk = cdiv(M * (o.d / 4), kRedThreads), n_v = cdiv(o.d, 64) * cdiv(M, 16);
   if (o.hd == 128)
@@ -859,9 +1040,9 @@ hipError_t gemm_qkv(int dtype, const void* A, int lda, const void* Wqkv, int M, 
   const int bm = tile_rows(GEMM_KIND_QKV, M, N, K);
   if (o.hd == 128)
     return dtype ? launch<bf16_t, EPI_QKV, 128>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s)
-                 : launch<float, EPI_QKV, 128>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s);
+                 : launch_f32<EPI_QKV, 128>(A, lda, Wqkv, K, M, N, K, ep, s);
   return dtype ? launch<bf16_t, EPI_QKV, 64>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s)
-               : launch<float, EPI_QKV, 64>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s);
+               : launch_f32<EPI_QKV, 64>(A, lda, Wqkv, K, M, N, K, ep, s);
 }
 
 }  // namespace dllm
