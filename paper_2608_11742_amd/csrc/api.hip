@@ -475,7 +475,7 @@ dllm_status forward_impl(dllm_model* m, const int32_t* tokens, int32_t batch, in
   }
   {
     ProfScope ps(m, s, DLLM_PROF_LMHEAD_MERGE);
-    TRY_HIP(lmhead_merge(R, d.vocab, to_out(*out), base + L.lm, s), "lm head merge");
+    TRY_HIP(lmhead_merge(dt, R, d.vocab, to_out(*out), base + L.lm, s), "lm head merge");
   }
   if (probe && probe->n > 0) {
     ProfScope ps(m, s, DLLM_PROF_OTHER);
@@ -533,7 +533,7 @@ dllm_status vocab_entropy_topk(const void* hidden, const void* w_lm, int32_t R, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   TRY_HIP(lmhead_partials(dtype, hidden, w_lm, R, d, vocab, row_scale, nullptr, R, R, scale, mask_id, ws, s),
           "vocab_entropy_topk");
-  return hip_check(lmhead_merge(R, vocab, to_out(*out), ws, s), "vocab_entropy_topk merge");
+  return hip_check(lmhead_merge(dtype, R, vocab, to_out(*out), ws, s), "vocab_entropy_topk merge");
 }
 
 // ---------------------------------------------------------------- allocation-free LM head

@@ -108,7 +108,7 @@ size_t lmhead_workspace(int R, int V);
 hipError_t lmhead_partials(int dtype, const void* h, const void* w, int R, int d, int V, const float* row_scale,
                            const int32_t* rs_idx, int rs_n, int rs_lim, float scale, int mask_id, void* ws,
                            hipStream_t s);
-hipError_t lmhead_merge(int R, int V, const StatsOut& out, void* ws, hipStream_t s);
+hipError_t lmhead_merge(int dtype, int R, int V, const StatsOut& out, void* ws, hipStream_t s);
 hipError_t probe_logits(int dtype, const void* h, const void* w, int d, int V, int R, const int32_t* row,
                         const int32_t* tok, int n, const float* row_scale, const int32_t* rs_idx, int n_pos,
                         int rs_lim, float scale, float* out, hipStream_t s);

@@ -2,10 +2,10 @@
 // needs (entropy, log-sum-exp, max logit, argmax, top-K).  The [R][V] logits
 // never leave the chip.
 //
-// Pass 1 (lmhead_kernel): a workgroup owns 128 hidden rows and one slice of
-// the vocabulary.  For each 256-token vocabulary tile it runs the MFMA
-// mainloop, scales the logits, stages the 128x256 fp32 tile in LDS and lets
-// 4 threads per row scan 64 logits each, updating a running max m,
+// Pass 1 (lmhead_kernel): a workgroup owns a tile of hidden rows and one
+// slice of the vocabulary.  For each vocabulary tile it runs the MFMA
+// mainloop, scales the logits, stages them as fp32 in LDS and lets 2 or 4
+// threads per row scan 32 or 64 logits each, updating a running max m,
 // s = sum exp(l - m), t = sum exp(l - m) (l - m) (m and t in log2 units
 // while scanning, natural units in the partials) and a sorted top-16.  At
 // the end of its slice every thread writes its partial state.
@@ -23,33 +23,40 @@ namespace dllm {
 
 namespace {
 
-constexpr int kCols = 256;                               // vocabulary tile
-constexpr int kThreads = 512;
 constexpr int kK = DLLM_TOPK_REG;
-constexpr int kSegCols = 64;                             // logits per scan thread per pass
-constexpr int kSegStride = kSegCols * 4 + 16;            // padded segment bytes
 // Workgroups of a launch: one per CU (the 256-row tile's LDS holds one), each
 // walking its vocabulary slice.  Two rounds of half-length slices measured
 // 4-6% slower at 512 and 4096 rows: every slice pays its first tile, where
 // the empty top-16 lists make many logits candidates, and the merge folds
 // twice the partials.
-constexpr int kTargetWg = 256;
+// The small tile's workgroups hold 54 KB of LDS each, two run on a CU, and one
+// streams its weights while the other scans.
+constexpr int kTargetWg = 256, kTargetWgSmall = 512;
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
-// BM rows per workgroup: 256 (8 waves of 64 x 128, the projection GEMMs'
-// tile) when there are more than 128 rows, else 128 (8 waves of 64 x 64).
-// kSegs scan threads per row, each scanning 64 logits per pass; a pass
-// stages kSegs * 64 columns of the fp32 logit tile in LDS.
+// Tiles of BM rows by COLS vocabulary entries: 256 x 256 (8 waves of 64 x 128,
+// the projection GEMMs' tile), 128 x 256 (8 waves of 64 x 64) and 64 x 128 (4
+// waves of 32 x 64); lm_tile picks one.
+// kSegs scan threads per row, each scanning kSegCols logits per pass; a pass
+// stages kSegs * kSegCols columns of the fp32 logit tile in LDS.
 // The MFMA blocks are computed transposed (TRANS), so that a lane holds 4
 // consecutive logits of one row and stages them with one 16-byte LDS write;
-// bf16 256-row tiles take the two-group mainloop of the projections;
-// 128-row tiles (few rows: the vocabulary streams from HBM) the early-release
+// bf16 256-row tiles take the two-group mainloop of the projections; the
+// smaller ones (few rows: the vocabulary streams from HBM) the early-release
 // TileMma schedule.
-template <typename T, int BM>
+template <typename T, int BM_>
 struct LmCfg {
+  using Type = T;
+  static constexpr int BM = BM_;
+  static constexpr int kCols = BM == 64 ? 128 : 256;         // vocabulary tile
+  static constexpr int kThreads = BM == 64 ? 256 : 512;
+  static constexpr int kMinBlocks = BM == 64 ? 2 : 1;
+  static constexpr int kWavesM = BM == 256 ? 4 : 2, kWavesN = BM == 128 ? 4 : 2;
   using TM = std::conditional_t<BM == 256 && std::is_same_v<T, bf16_t>, PingPongMma<T, true>,
-                                TileMma<T, BM, kCols, BM == 256 ? 4 : 2, BM == 256 ? 2 : 4, true, BM == 128>>;
+                                TileMma<T, BM, kCols, kWavesM, kWavesN, true, BM != 256>>;
   static constexpr int kSegs = kThreads / BM;
+  static constexpr int kSegCols = BM == 64 ? 32 : 64;        // logits per scan thread per pass
+  static constexpr int kSegStride = kSegCols * 4 + 16;       // padded segment bytes
   static constexpr int kPassCols = kSegs * kSegCols;
   static constexpr int kPasses = kCols / kPassCols;
   static constexpr int kRowStride = kSegs * kSegStride + 16;   // padded row bytes
@@ -57,9 +64,18 @@ struct LmCfg {
   static constexpr int kSmem = TM::kSmem > kStageBytes ? TM::kSmem : kStageBytes;
   static constexpr int kBoundRank = kK / kSegs - 1;            // see the pruning bound below
   static_assert(kPasses == 1 || kPassCols == TM::kWTN, "a pass is the whole tile or one wave column");
+  static_assert(kSegs * (kSegCols / 8) >= kK, "the seed bound covers the top 16");
 };
 
-int tile_rows(int R) { return R > 128 ? 256 : 128; }
+// Row tile of an LM head over R rows and V vocabulary entries.
+int lm_tile(int dtype, int R, int V) {
+  const bool few = cdiv(R, 128) * cdiv(V, 256) < kTargetWg / 2;   // 128 x 256 tiles would leave half the CUs idle
+  if (R <= 64 || few) return 64;
+  if (dtype) return R > 128 ? 256 : 128;
+  // fp32: the matrix cores bound every tile; the largest keeps the partials
+  // of very many rows (2 a row instead of 4) small
+  return R > 32768 ? 256 : 128;
+}
 
 struct Partials {
   float* m;
@@ -86,7 +102,8 @@ __device__ __forceinline__ void topk_insert(float (&tv)[kK], int (&ti)[kK], floa
 }
 
 template <typename T, int BM>
-__global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict__ Hs, const T* __restrict__ W, int R,
+__global__ __launch_bounds__((LmCfg<T, BM>::kThreads), (LmCfg<T, BM>::kMinBlocks)) void lmhead_kernel(
+    const T* __restrict__ Hs, const T* __restrict__ W, int R,
                                                              int d, int V, const float* __restrict__ row_scale,
                                                              const int32_t* __restrict__ rs_idx, int rs_n, int rs_lim,
                                                              float scale, int mask_id, int row_tiles,
@@ -94,7 +111,8 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
                                                              int vtiles, Partials part) {
   using Cfg = LmCfg<T, BM>;
   using TM = typename Cfg::TM;
-  constexpr int kSegs = Cfg::kSegs, kRowStride = Cfg::kRowStride;
+  constexpr int kSegs = Cfg::kSegs, kRowStride = Cfg::kRowStride, kCols = Cfg::kCols;
+  constexpr int kSegCols = Cfg::kSegCols, kSegStride = Cfg::kSegStride;
   __shared__ __attribute__((aligned(16))) uint8_t smem[Cfg::kSmem];
 
   // XCD-contiguous ids, walked in groups of 8 row tiles: the 32 workgroups an
@@ -191,7 +209,7 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
 #pragma unroll
     for (int pass = 0; pass < Cfg::kPasses; ++pass) {
     // stage this pass's scaled logits: LDS row r, pass column c at
-    // r * kRowStride + (c / 64) * kSegStride + (c % 64) * 4
+    // r * kRowStride + (c / kSegCols) * kSegStride + (c % kSegCols) * 4
     if (Cfg::kPasses == 1 || wn == pass) {
 #pragma unroll
       for (int mi = 0; mi < TM::kFM; ++mi)
@@ -200,11 +218,12 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
           // (transposed blocks) row 16 mi + lane % 16, columns 16 ni + 4 (lane / 16) + 0..3
           const int r = wm * TM::kWTM + mi * 16 + (lane & 15);
           const int c = wn * TM::kWTN + ni * 16 + 4 * (lane >> 4) - pass * Cfg::kPassCols;
-          *reinterpret_cast<f32x4*>(smem + r * kRowStride + (c >> 6) * kSegStride + (c & 63) * 4) = acc[mi][ni];
+          *reinterpret_cast<f32x4*>(smem + r * kRowStride + (c / kSegCols) * kSegStride + (c % kSegCols) * 4) =
+              acc[mi][ni];
         }
     }
     __syncthreads();
-    // scan 64 logits of row srow: running statistics, and a bit mask of the
+    // scan kSegCols logits of row srow: running statistics, and a bit mask of the
     // logits that may beat the pruning bound (candidates for the top 16)
     const uint8_t* base = smem + srow * kRowStride + sseg * kSegStride;
     const int c0 = n0 + pass * Cfg::kPassCols + sseg * kSegCols;
@@ -212,7 +231,7 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
     if (vt == t_begin && pass == 0) {
       // The slice's top-16 lists are still empty, which would make every
       // logit a candidate.  Seed the bound instead: each thread takes the
-      // smallest of the maxima of its 8 groups of 8 logits (8 logits are at
+      // smallest of the maxima of its groups of 8 logits (as many logits are at
       // least that large), the row the smallest over its kSegs threads, so at
       // least 16 logits of the row are at least as large as the bound and no
       // smaller logit can reach the row's top 16.
@@ -313,7 +332,8 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
     __syncthreads();
     }
     if constexpr (!kListInMemory) refresh_bound();
-    if (kListInMemory && own_row) {
+    const bool last = vt + 1 == t_end;
+    if (own_row && (kListInMemory || last)) {
       part.m[slot] = m * kLn2;   // natural units in the partials
       part.s[slot] = s;
       part.t[slot] = t * kLn2;
@@ -324,47 +344,68 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_kernel(const T* __restrict
       }
     }
   }
-  if (own_row && !kListInMemory) {
-    part.m[slot] = m * kLn2;
-    part.s[slot] = s;
-    part.t[slot] = t * kLn2;
-    {
+}
+
+// Sort the 64 lanes' (value, id) pairs by better(), best in lane 0.
+__device__ __forceinline__ void wave_sort(float& v, int& i) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-      for (int k = 0; k < kK; ++k) {
-        part.tv[slot * kK + k] = tv[k];
-        part.ti[slot * kK + k] = ti[k];
-      }
+  for (int size = 2; size <= 64; size <<= 1)
+#pragma unroll
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      const float w = __shfl_xor(v, d, 64);
+      const int j = __shfl_xor(i, d, 64);
+      // lanes of even blocks of `size` sort best first, odd ones best last
+      const bool keep_better = ((lane & size) == 0) == ((lane & d) == 0);
+      const bool other = better(w, j, v, i) == keep_better;
+      if (other && (w != v || j != i)) { v = w; i = j; }
     }
-  }
 }
 
 // One workgroup of W = blockDim.x / 64 waves per row (W grows with the number
-// of partials, so that rows with many vocabulary slices merge in parallel).
-// Every lane folds a strided share of the row's partials into (S, T) and a
-// sorted top-16; each wave merges its lanes' lists into its own top-16 by
-// repeated wave-wide argmax; the waves' lists and sums meet in LDS and wave 0
-// merges them the same way.
+// of partials).  The row's top 16 lie in few of its partials' sorted lists: a
+// wave sorts its lanes' best list heads, and the 16th of them is a bound that
+// at least 16 logits of the row reach, so only the entries no worse than the
+// best wave's bound are candidates (a few hundred of P * 16).  They are
+// gathered in LDS and wave 0 sorts them, 48 at a time behind the best 16 so far.
+// Latency bound.  32 rows of 1024 partials 44 -> 13 us, of 2048 64 -> 23
+// against folding every list into a per-lane top 16.  Ranking heads and
+// candidates by counting instead of sorting took 28 us for 2048; merging the
+// lists of a row's scan threads in pass 1 took as long there as it saved here.
 __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsOut out) {
-  constexpr int kMaxW = 8;
-  __shared__ float red_m[kMaxW], red_s[kMaxW], red_t[kMaxW];
-  __shared__ float lv[kMaxW][kK];
-  __shared__ int li[kMaxW][kK];
+  constexpr int kMaxW = 8, kCap = 1024;
+  __shared__ float red_m[kMaxW], red_s[kMaxW], red_t[kMaxW], bound_v[kMaxW];
+  __shared__ int bound_i[kMaxW];
+  __shared__ float cv[kCap];
+  __shared__ int ci[kCap];
+  __shared__ int n_cand;
   const int row = blockIdx.x;
   const int W = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (row >= R) return;
   const size_t base = size_t(row) * part.P;
-  float M = -INFINITY;
-  for (int p = threadIdx.x; p < part.P; p += blockDim.x) M = fmaxf(M, part.m[base + p]);
+  // this thread's partials: their maximum and their best list head
+  float M = -INFINITY, hv = -INFINITY;
+  int hi = 0x7fffffff;
+  for (int p = threadIdx.x; p < part.P; p += blockDim.x) {
+    M = fmaxf(M, part.m[base + p]);
+    const float v = part.tv[(base + p) * kK];
+    const int i = part.ti[(base + p) * kK];
+    if (better(v, i, hv, hi)) { hv = v; hi = i; }
+  }
   M = wave_max(M);
+  wave_sort(hv, hi);
+  if (lane == kK - 1) { bound_v[wave] = hv; bound_i[wave] = hi; }
   if (lane == 0) red_m[wave] = M;
+  if (threadIdx.x == 0) n_cand = 0;
   __syncthreads();
   M = red_m[0];
-  for (int w = 1; w < W; ++w) M = fmaxf(M, red_m[w]);
+  float bv = bound_v[0];
+  int bi = bound_i[0];
+  for (int w = 1; w < W; ++w) {
+    M = fmaxf(M, red_m[w]);
+    if (better(bound_v[w], bound_i[w], bv, bi)) { bv = bound_v[w]; bi = bound_i[w]; }
+  }
   float S = 0.f, Tt = 0.f;
-  float tv[kK];
-  int ti[kK];
-#pragma unroll
-  for (int k = 0; k < kK; ++k) { tv[k] = -INFINITY; ti[k] = 0x7fffffff; }
   for (int p = threadIdx.x; p < part.P; p += blockDim.x) {
     const float mp = part.m[base + p];
     if (mp == -INFINITY) continue;  // a partial that saw no valid logit
@@ -374,54 +415,44 @@ __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsO
     Tt += w * (part.t[base + p] + (mp - M) * sp);
     const float* pv = part.tv + (base + p) * kK;
     const int32_t* pi = part.ti + (base + p) * kK;
-#pragma unroll
-    for (int k = 0; k < kK; ++k) {
+    for (int k = 0; k < kK; ++k) {   // sorted: the first entry below the bound ends the list
       const float v = pv[k];
       const int i = pi[k];
-      if (better(v, i, tv[kK - 1], ti[kK - 1])) topk_insert(tv, ti, v, i);
+      if (i == 0x7fffffff || better(bv, bi, v, i)) break;
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < kCap) { cv[at] = v; ci[at] = i; }
     }
   }
   S = wave_sum(S);
   Tt = wave_sum(Tt);
-  // 64-way merge of the lanes' sorted lists: the wave-wide best head is taken n times
-  auto merge_lanes = [&](int n, auto&& emit) {
-    for (int k = 0; k < n; ++k) {
-      float v = tv[0];
-      int i = ti[0];
-      wave_argmax(v, i);
-      emit(k, v, i);
-      if (ti[0] == i) {  // ids are unique: exactly one lane owns the winner; pop it
-#pragma unroll
-        for (int j = 0; j < kK - 1; ++j) { tv[j] = tv[j + 1]; ti[j] = ti[j + 1]; }
-        tv[kK - 1] = -INFINITY;
-        ti[kK - 1] = 0x7fffffff;
-      }
-    }
+  if (lane == 0) { red_s[wave] = S; red_t[wave] = Tt; }
+  __syncthreads();
+  if (wave != 0) return;
+  S = red_s[0];
+  Tt = red_t[0];
+  for (int w = 1; w < W; ++w) { S += red_s[w]; Tt += red_t[w]; }
+  // sort the candidates (or, where ties filled the buffer, every entry): the
+  // ids are unique, so the order does not depend on how they were gathered
+  const bool all = n_cand > kCap;
+  const int n = all ? part.P * kK : n_cand;
+  auto entry = [&](int e, float& v, int& i) {
+    v = e >= n ? -INFINITY : all ? part.tv[base * kK + e] : cv[e];
+    i = e >= n ? 0x7fffffff : all ? part.ti[base * kK + e] : ci[e];
   };
-  if (W > 1) {
-    merge_lanes(kK, [&](int k, float v, int i) {
-      if (lane == 0) { lv[wave][k] = v; li[wave][k] = i; }
-    });
-    if (lane == 0) { red_s[wave] = S; red_t[wave] = Tt; }
-    __syncthreads();
-    if (wave != 0) return;
-    S = red_s[0];
-    Tt = red_t[0];
-    for (int w = 1; w < W; ++w) { S += red_s[w]; Tt += red_t[w]; }
-#pragma unroll
-    for (int k = 0; k < kK; ++k) {
-      tv[k] = lane < W ? lv[lane][k] : -INFINITY;
-      ti[k] = lane < W ? li[lane][k] : 0x7fffffff;
-    }
+  float v;
+  int i;
+  entry(lane, v, i);
+  wave_sort(v, i);
+  for (int e = 64; e < n; e += 64 - kK) {
+    if (lane >= kK) entry(e + lane - kK, v, i);
+    wave_sort(v, i);
   }
-  merge_lanes(out.k, [&](int k, float v, int i) {
-    if (lane == 0) {
-      out.topk_id[size_t(row) * out.k + k] = i;
-      out.topk_logit[size_t(row) * out.k + k] = v;
-      if (k == 0) out.argmax[row] = i;
-    }
-  });
+  if (lane < out.k) {
+    out.topk_id[size_t(row) * out.k + lane] = i;
+    out.topk_logit[size_t(row) * out.k + lane] = v;
+  }
   if (lane == 0) {
+    out.argmax[row] = i;
     const float logS = logf(S);
     out.lmax[row] = M;
     out.lse[row] = M + logS;
@@ -448,12 +479,18 @@ __global__ __launch_bounds__(256) void probe_kernel(const T* __restrict__ Hs, co
   if (lane == 0) out[p] = acc * scale * (row_scale ? row_scale[rs_idx ? min(max(rs_idx[r % n_pos], 0), rs_lim - 1) : r % n_pos] : 1.0f);
 }
 
-int slices_for(int R, int V) {
-  const int rt = cdiv(R, tile_rows(R)), vt = cdiv(V, kCols);
-  return std::max(1, std::min(vt, cdiv(kTargetWg, rt)));
+// Vocabulary slices: as many as one round of workgroups holds, or one more
+// where rounding up needs fewer tile times over all rounds.
+int slices_for(int bm, int R, int V) {
+  const int rt = cdiv(R, bm), vt = cdiv(V, bm == 64 ? 128 : 256), target = bm == 64 ? kTargetWgSmall : kTargetWg;
+  const int up = std::max(1, std::min(vt, cdiv(target, rt))), down = std::max(1, std::min(vt, target / rt));
+  auto tile_times = [&](int n) { return cdiv(rt * n, target) * cdiv(vt, n); };
+  return tile_times(up) < tile_times(down) ? up : down;
 }
 
-int partials_per_row(int R, int V) { return slices_for(R, V) * (kThreads / tile_rows(R)); }
+int partials_per_row(int bm, int R, int V) { return slices_for(bm, R, V) * (bm == 256 ? 2 : 4); }
+static_assert(LmCfg<bf16_t, 256>::kSegs == 2 && LmCfg<bf16_t, 128>::kSegs == 4 && LmCfg<bf16_t, 64>::kSegs == 4,
+              "partials_per_row");
 
 Partials carve(void* ws, int R, int P) {
   Partials pt;
@@ -471,7 +508,8 @@ Partials carve(void* ws, int R, int P) {
 }  // namespace
 
 size_t lmhead_workspace(int R, int V) {
-  const size_t P = size_t(partials_per_row(R, V));
+  size_t P = 0;
+  for (int dtype = 0; dtype < 2; ++dtype) P = std::max(P, size_t(partials_per_row(lm_tile(dtype, R, V), R, V)));
   return size_t(R) * P * (3 + 2 * kK) * 4 + 256;
 }
 
@@ -479,28 +517,31 @@ hipError_t lmhead_partials(int dtype, const void* h, const void* w, int R, int d
                            const int32_t* rs_idx, int rs_n, int rs_lim, float scale, int mask_id, void* ws,
                            hipStream_t s) {
   if (d <= 0 || d % (dtype ? 64 : 32)) return hipErrorInvalidValue;   // the mainloop runs stages in pairs
-  const int ns = slices_for(R, V);
-  const int bm = tile_rows(R);
-  const int rt = cdiv(R, bm), vt = cdiv(V, kCols);
-  Partials part = carve(ws, R, partials_per_row(R, V));
-  const int grid = rt * ns;
-  auto go = [&](auto kern, auto* hp, auto* wp) {
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, hp, wp, R, d, V, row_scale, rs_idx, rs_n, rs_lim,
-                       scale, mask_id, rt, ns, vt, part);
+  const int bm = lm_tile(dtype, R, V);
+  auto go = [&](auto cfg, auto kern) {
+    using Cfg = decltype(cfg);
+    using T = typename Cfg::Type;
+    const int ns = slices_for(bm, R, V), rt = cdiv(R, bm), vt = cdiv(V, Cfg::kCols);
+    const Partials part = carve(ws, R, partials_per_row(bm, R, V));
+    hipLaunchKernelGGL(kern, dim3(rt * ns), dim3(Cfg::kThreads), 0, s, static_cast<const T*>(h),
+                       static_cast<const T*>(w), R, d, V, row_scale, rs_idx, rs_n, rs_lim, scale, mask_id, rt, ns, vt,
+                       part);
   };
-  const bf16_t* hb = static_cast<const bf16_t*>(h);
-  const bf16_t* wb = static_cast<const bf16_t*>(w);
-  const float* hf = static_cast<const float*>(h);
-  const float* wf = static_cast<const float*>(w);
-  if (dtype)
-    bm == 256 ? go(lmhead_kernel<bf16_t, 256>, hb, wb) : go(lmhead_kernel<bf16_t, 128>, hb, wb);
-  else
-    bm == 256 ? go(lmhead_kernel<float, 256>, hf, wf) : go(lmhead_kernel<float, 128>, hf, wf);
+  if (dtype) {
+    if (bm == 256) go(LmCfg<bf16_t, 256>{}, lmhead_kernel<bf16_t, 256>);
+    else if (bm == 128) go(LmCfg<bf16_t, 128>{}, lmhead_kernel<bf16_t, 128>);
+    else go(LmCfg<bf16_t, 64>{}, lmhead_kernel<bf16_t, 64>);
+  } else {
+    if (bm == 256) go(LmCfg<float, 256>{}, lmhead_kernel<float, 256>);
+    else if (bm == 128) go(LmCfg<float, 128>{}, lmhead_kernel<float, 128>);
+    else go(LmCfg<float, 64>{}, lmhead_kernel<float, 64>);
+  }
   return hipGetLastError();
 }
 
-hipError_t lmhead_merge(int R, int V, const StatsOut& out, void* ws, hipStream_t s) {
-  Partials part = carve(ws, R, partials_per_row(R, V));
+hipError_t lmhead_merge(int dtype, int R, int V, const StatsOut& out, void* ws, hipStream_t s) {
+  const int bm = lm_tile(dtype, R, V);
+  const Partials part = carve(ws, R, partials_per_row(bm, R, V));
   const int waves = std::min(8, std::max(1, cdiv(part.P, 128)));
   hipLaunchKernelGGL(merge_kernel, dim3(R), dim3(64 * waves), 0, s, part, R, out);
   return hipGetLastError();

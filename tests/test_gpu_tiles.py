@@ -37,3 +37,77 @@ def test_forward_f32_row_tiles(P, hd, B_, S):
     ref = softmax_stats(om.forward_logits(toks, w_np, shape, lm_pos, scale=2.0).reshape(-1, shape.vocab), 16)
     print(compare_stats(out.numpy(), ref, 1e-4, label=f"f32 hd {hd} {B_} x {S}"))
     model.close()
+
+
+# LM head: 64-, 128- and 256-row tiles, rows and vocabularies around a tile
+# edge, one slice and many, the merge of 1 to 8 waves of partials
+@pytest.mark.parametrize("dtype,R,d,V", [
+    ("bf16", 64, 128, 127), ("bf16", 65, 128, 129), ("bf16", 3, 64, 33000), ("bf16", 130, 64, 40000),
+    ("f32", 64, 64, 1024), ("f32", 65, 64, 33000), ("f32", 300, 32, 2049), ("f32", 33000, 32, 260)])
+def test_lm_head_tiles(P, dtype, R, d, V):
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    h = synth.hidden_np(11, "h", (R, d), dtype=dtype)
+    w = synth.weight_np(12, "w", (V, d), std=0.1, dtype=dtype)
+    mask = V // 2
+    out = P.Stats(R, 16, device=DEV).fill_(float("nan"))
+    ws = torch.full((P.vocab_entropy_topk_workspace_bytes(R, V),), 255, dtype=torch.uint8, device=DEV)
+    P.vocab_entropy_topk(torch.from_numpy(h).to(DEV).to(td), torch.from_numpy(w).to(DEV).to(td), out, ws, scale=2.0,
+                         mask_id=mask)
+    torch.cuda.synchronize()
+    logits = 2.0 * (h.astype(np.float64) @ w.astype(np.float64).T)
+    logits[:, mask] = -np.inf
+    print(compare_stats(out.numpy(), softmax_stats(logits, 16), 1e-4 if dtype == "f32" else 1e-3,
+                        label=f"lm head {dtype} {R} x {V}"))
+
+
+@pytest.mark.parametrize("R,V,k", [(2, 40000, 16), (70, 33000, 5), (1, 12, 16)])
+def test_lm_head_of_equal_logits(P, R, V, k):
+    """Ties everywhere: the ids ascend, and every partial's list reaches the
+    merge's bound.  With fewer tokens than ranks the rest stay empty."""
+    out = P.Stats(R, k, device=DEV).fill_(float("nan"))
+    ws = torch.empty(P.vocab_entropy_topk_workspace_bytes(R, V), dtype=torch.uint8, device=DEV)
+    P.vocab_entropy_topk(torch.zeros(R, 64, dtype=torch.bfloat16, device=DEV),
+                         torch.ones(V, 64, dtype=torch.bfloat16, device=DEV), out, ws, mask_id=3)
+    got = out.numpy()
+    want = [i for i in range(min(V, 17)) if i != 3][:k]
+    assert (got["topk_id"][:, :len(want)] == want).all() and (got["topk_logit"][:, :len(want)] == 0).all()
+    assert np.isneginf(got["topk_logit"][:, len(want):]).all()
+    assert (got["argmax"] == 0).all() and np.allclose(got["H"], np.log(V - 1), atol=1e-4)
+
+
+# scheduler: rows one below, at and one above the commit kernel's 256 threads
+# and its limit of 1024, every kept row in order; positions past the sequence
+# are clamped, the last row that lands on a token wins
+@pytest.mark.parametrize("n_m", [1, 63, 64, 65, 255, 256, 257, 1000, 1024])
+@pytest.mark.parametrize("shift", [0, 5])
+def test_commit_rows(P, n_m, shift):
+    rng = np.random.default_rng(n_m)
+    seq, k = n_m + 7, 4
+    base = P.Stats(n_m, k, device=DEV)
+    f = {n: rng.normal(size=getattr(base, n).shape).astype(np.float32) for n in ("H", "lse", "lmax", "topk_logit")}
+    f["lmax"] = f["lse"] - 1.0 - np.abs(f["lmax"])
+    f["lmax"][rng.random(n_m) < 0.4] = f["lse"][0] = 0.0
+    f["lse"][f["lmax"] == 0.0] = 0.05
+    i = {n: rng.integers(0, 9000, getattr(base, n).shape).astype(np.int32) for n in ("argmax", "topk_id")}
+    for n, v in {**f, **i}.items():
+        getattr(base, n).copy_(torch.from_numpy(v))
+    pos = np.arange(7 + shift, seq + shift, dtype=np.int32)
+    tokens = rng.integers(0, 9000, seq).astype(np.int32)
+    t, m = torch.from_numpy(tokens).to(DEV), torch.from_numpy(pos).to(DEV)
+    one = lambda n: torch.full((n,), -7, dtype=torch.int32, device=DEV)
+    n_out, com, n_com = one(1), one(n_m), one(1)
+    P.rps_commit(t, m, n_m, base, 0.9, n_out, com, n_com)
+    conf = np.exp((f["lmax"] - f["lse"]).astype(np.float64))
+    sel = conf >= 0.9
+    if not sel.any():
+        sel[np.argmax(conf)] = True
+    want = tokens.copy()
+    for j in np.flatnonzero(sel):
+        want[min(pos[j], seq - 1)] = i["argmax"][j]
+    keep = ~sel
+    assert n_out.item() == keep.sum() and n_com.item() == sel.sum()
+    assert (com.cpu().numpy()[:sel.sum()] == pos[sel]).all() and (t.cpu().numpy() == want).all()
+    assert (m.cpu().numpy()[:keep.sum()] == pos[keep]).all()
+    got = base.numpy()
+    for n, v in {**f, **i}.items():
+        assert (got[n][:keep.sum()] == v[keep]).all(), n
