@@ -47,6 +47,10 @@ __global__ __launch_bounds__(kT) void select_kernel(StatsIn st, const int32_t* _
   __shared__ int red_i[4];
   __shared__ int chosen[RPS_MAX_PIVOTS];
   __shared__ float band[2];
+  __shared__ float piv_logit[RPS_MAX_PIVOTS][DLLM_MAX_TOPK], piv_lse[RPS_MAX_PIVOTS];
+  __shared__ int piv_id[RPS_MAX_PIVOTS][DLLM_MAX_TOPK], piv_pos[RPS_MAX_PIVOTS];
+  __shared__ uint8_t reach[RPS_MAX_PIVOTS][DLLM_MAX_TOPK];
+  __shared__ rps_plan pl;
   const int tid = threadIdx.x;
   const int kmax = min(prm.k_max, st.k);
 
@@ -113,41 +117,59 @@ __global__ __launch_bounds__(kT) void select_kernel(StatsIn st, const int32_t* _
     __syncthreads();
   }
 
-  if (tid != 0) return;
-  // adaptive candidate sets: v in T_{i*} with p(v) >= r P^max, rank order, capped
-  rps_plan& pl = *plan;   // written in place (a private copy would live in scratch memory)
-  pl.n_pivots = 0;
-  pl.n_branch = 0;
-  for (int i = 0; i < RPS_MAX_PIVOTS; ++i) pl.pivot_row[i] = pl.pivot_pos[i] = pl.n_cand[i] = -1;
-  for (int i = 0; i < RPS_MAX_BRANCH; ++i) {
-    pl.br_pivot[i] = pl.br_row[i] = pl.br_pos[i] = pl.br_token[i] = -1;
-    pl.br_logp[i] = 0.f;
-  }
-  const int cap = min(prm.max_branch, RPS_MAX_BRANCH);
-  for (int rnd = 0; rnd < n_piv; ++rnd) {
-    const int j = chosen[rnd];
-    if (j < 0) break;
-    const float lmax = st.lmax[j], lse = st.lse[j];
-    int cnt = 0;
-    for (int k = 0; k < kmax && cnt < prm.n_cand && pl.n_branch + cnt < cap; ++k) {
+  // adaptive candidate sets: v in T_{i*} with p(v) >= r P^max, rank order,
+  // capped.  One thread per (pivot, rank) loads and tests, thread 0 counts in
+  // LDS and all write the plan: a chain of global loads in one thread took
+  // half of this kernel's time.
+  static_assert(RPS_MAX_PIVOTS * DLLM_MAX_TOPK == kT, "one thread per pivot and rank");
+  {
+    const int rnd = tid / DLLM_MAX_TOPK, k = tid % DLLM_MAX_TOPK;
+    const int j = rnd < n_piv ? chosen[rnd] : -1;
+    if (j >= 0 && k < kmax) {
       const float lg = st.topk_logit[size_t(j) * st.k + k];
-      if (!(expf(lg - lmax) >= prm.r)) break;   // p(v) / P^max is non-increasing in rank
-      ++cnt;
-    }
-    if (cnt < 2) continue;
-    const int p = pl.n_pivots++;
-    pl.pivot_row[p] = j;
-    pl.pivot_pos[p] = m_pos[j];
-    pl.n_cand[p] = cnt;
-    for (int k = 0; k < cnt; ++k) {
-      const int b = pl.n_branch++;
-      pl.br_pivot[b] = p;
-      pl.br_row[b] = j;
-      pl.br_pos[b] = m_pos[j];
-      pl.br_token[b] = st.topk_id[size_t(j) * st.k + k];
-      pl.br_logp[b] = st.topk_logit[size_t(j) * st.k + k] - lse;
+      piv_logit[rnd][k] = lg;
+      piv_id[rnd][k] = st.topk_id[size_t(j) * st.k + k];
+      reach[rnd][k] = expf(lg - st.lmax[j]) >= prm.r;   // p(v) / P^max is non-increasing in rank
+      if (k == 0) {
+        piv_lse[rnd] = st.lse[j];
+        piv_pos[rnd] = m_pos[j];
+      }
     }
   }
+  if (tid < RPS_MAX_PIVOTS) pl.pivot_row[tid] = pl.pivot_pos[tid] = pl.n_cand[tid] = -1;
+  if (tid < RPS_MAX_BRANCH) {
+    pl.br_pivot[tid] = pl.br_row[tid] = pl.br_pos[tid] = pl.br_token[tid] = -1;
+    pl.br_logp[tid] = 0.f;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int np = 0, nb = 0;
+    const int cap = min(prm.max_branch, RPS_MAX_BRANCH);
+    for (int rnd = 0; rnd < n_piv; ++rnd) {
+      const int j = chosen[rnd];
+      if (j < 0) break;
+      int cnt = 0;
+      for (int k = 0; k < kmax && cnt < prm.n_cand && nb + cnt < cap && reach[rnd][k]; ++k) ++cnt;
+      if (cnt < 2) continue;
+      pl.pivot_row[np] = j;
+      pl.pivot_pos[np] = piv_pos[rnd];
+      pl.n_cand[np] = cnt;
+      for (int k = 0; k < cnt; ++k, ++nb) {
+        pl.br_pivot[nb] = np;
+        pl.br_row[nb] = j;
+        pl.br_pos[nb] = piv_pos[rnd];
+        pl.br_token[nb] = piv_id[rnd][k];
+        pl.br_logp[nb] = piv_logit[rnd][k] - piv_lse[rnd];
+      }
+      ++np;
+    }
+    pl.n_pivots = np;
+    pl.n_branch = nb;
+  }
+  __syncthreads();
+  static_assert(sizeof(rps_plan) % 4 == 0, "plan words");
+  for (int w = tid; w < int(sizeof(rps_plan) / 4); w += kT)
+    reinterpret_cast<int*>(plan)[w] = reinterpret_cast<const int*>(&pl)[w];
 }
 
 __global__ __launch_bounds__(kT) void branch_kernel(const int32_t* __restrict__ tokens, int seq,
@@ -180,7 +202,9 @@ __global__ __launch_bounds__(kT) void packed_branch_kernel(const int32_t* __rest
   out[seq + size_t(b) * B + s] = v;
 }
 
-__global__ __launch_bounds__(kT) void score_kernel(StatsIn anc, StatsIn br, int branch_offset, int n_m,
+// one wave per branch
+constexpr int kScoreT = RPS_MAX_BRANCH * kWave;
+__global__ __launch_bounds__(kScoreT) void score_kernel(StatsIn anc, StatsIn br, int branch_offset, int n_m,
                                                    const rps_plan* __restrict__ plan,
                                                    const float* __restrict__ anchor_logit, float lambda,
                                                    float* __restrict__ scores, float* __restrict__ deltas,
@@ -189,7 +213,7 @@ __global__ __launch_bounds__(kT) void score_kernel(StatsIn anc, StatsIn br, int 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nb = n_m > 1 ? plan->n_branch : 0;
   const float inv_n = n_m > 1 ? 1.0f / float(n_m - 1) : 0.f;
-  for (int b = wave; b < nb; b += kT / kWave) {
+  for (int b = wave; b < nb; b += kScoreT / kWave) {
     const int row = plan->br_row[b];
     const float* Hb = br.H + size_t(branch_offset + b) * n_m;
     float dsum = 0.f, hsum = 0.f;
@@ -246,23 +270,47 @@ __device__ void commit_compact(int32_t* __restrict__ tokens, int seq, int32_t* _
                                StatsOut base, StatsIn src, const uint8_t* sel, int* pre, int s_drop, int s_nc,
                                int32_t* __restrict__ n_m_out, int32_t* __restrict__ committed,
                                int32_t* __restrict__ n_committed) {
-  const int tid = threadIdx.x;
+  __shared__ int cnt[2][kT / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int K = base.k;
-  // exclusive prefix sums of selected rows (commit order) and of kept rows (new index)
-  if (tid == 0) {
-    int cs = 0, ks = 0;
-    for (int j = 0; j < n_m; ++j) {
-      const bool keep = j != s_drop && !sel[j];
-      if (sel[j]) {
-        committed[s_nc + cs] = m_pos[j];
-        tokens[min(max(m_pos[j], 0), seq - 1)] = src.argmax[j];
-        ++cs;
-      }
-      pre[j] = keep ? ks++ : -1;
+  // exclusive prefix sums of selected rows (commit order) and of kept rows
+  // (new index), kT rows at a time from ballots; one thread walking the rows
+  // took 25 us for 256 of them
+  int cs = 0, ks = 0;
+  bool outside = false;
+  for (int r0 = 0; r0 < n_m; r0 += kT) {
+    const int j = r0 + tid;
+    const bool c = j < n_m && sel[j], keep = j < n_m && j != s_drop && !sel[j];
+    const unsigned long long bc = __ballot(c), bk = __ballot(keep), below = (1ull << lane) - 1;
+    if (lane == 0) {
+      cnt[0][wave] = __popcll(bc);
+      cnt[1][wave] = __popcll(bk);
     }
+    __syncthreads();
+    int ci = cs + __popcll(bc & below), ki = ks + __popcll(bk & below);
+    for (int w = 0; w < kT / kWave; ++w) {
+      if (w < wave) { ci += cnt[0][w]; ki += cnt[1][w]; }
+      cs += cnt[0][w];
+      ks += cnt[1][w];
+    }
+    if (c) {
+      const int p = m_pos[j];
+      committed[s_nc + ci] = p;
+      outside = outside || p < 0 || p >= seq;
+      if (p >= 0 && p < seq) tokens[p] = src.argmax[j];
+    }
+    if (j < n_m) pre[j] = keep ? ki : -1;
+    __syncthreads();
+  }
+  if (tid == 0) {
     *n_m_out = ks;
     *n_committed = s_nc + cs;
   }
+  // positions outside the sequence are clamped; several rows may then write
+  // one token, in row order
+  if (__syncthreads_or(outside) && tid == 0)
+    for (int j = 0; j < n_m; ++j)
+      if (sel[j]) tokens[min(max(m_pos[j], 0), seq - 1)] = src.argmax[j];
   __syncthreads();
   // compaction (possibly in place): each round reads its rows before writing them
   for (int r0 = 0; r0 < n_m; r0 += kT) {
@@ -426,7 +474,7 @@ hipError_t rps_branches_packed(const int32_t* tokens, int seq, const rps_plan* p
 hipError_t rps_score(const StatsOut& anchor, const StatsOut& branches, int branch_offset, int n_m,
                      const rps_plan* plan, const float* anchor_logit, float lambda, float* scores, float* deltas,
                      rps_decision* dec, hipStream_t s) {
-  hipLaunchKernelGGL(score_kernel, dim3(1), dim3(kT), 0, s, to_in(anchor), to_in(branches), branch_offset, n_m, plan,
+  hipLaunchKernelGGL(score_kernel, dim3(1), dim3(kScoreT), 0, s, to_in(anchor), to_in(branches), branch_offset, n_m, plan,
                      anchor_logit, lambda, scores, deltas, dec);
   return hipGetLastError();
 }
