@@ -5,7 +5,7 @@
 //            head-major Q/K and transposed V
 // 256x256 output tiles, 8 waves of 64x128, bf16 MFMA, fp32 accumulate; fewer
 // rows take the smaller tile configurations below.  fp32 models take
-// gemm_f32_kernel.
+// gemm_direct_kernel.
 //
 // Few rows (a 512-row forward has 32 output tiles in the O and down
 // projections for 256 CUs): the K range is split into parts, every part
@@ -20,32 +20,24 @@ namespace dllm {
 
 namespace {
 
-// Tile configurations; Big and Small with waves of 64 x 128 (the epilogues' layout):
-// Big 256 x 256 with 8 waves (two per SIMD, one workgroup per CU); Small
-// 64 x 256 with 2 waves for GEMMs of at most kSmallM rows, where a 256-row
-// tile would mostly multiply clamped duplicate rows (two workgroups per CU).
-// EARLY: the TileMma schedule that hands a consumed ring slot to its next
+// Tile configurations of gemm_kernel; Big with waves of 64 x 128 (the
+// epilogues' layout): 256 x 256 with 8 waves (two per SIMD, one workgroup per
+// CU).  EARLY: the TileMma schedule that hands a consumed ring slot to its next
 // copies half a stage sooner (measured faster where the weights stream from
-// HBM at one tile per CU: 4-10% on the Quad and Mid launches, no change on
-// Small).
+// HBM at one tile per CU: 4-10% on the Quad and Mid launches).
 template <int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS, bool EARLY = false>
 struct GemmCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, kThreads = WM_ * WN_ * 64, kMinBlocks = MIN_BLOCKS;
   static constexpr bool kEarly = EARLY;
 };
 using Big = GemmCfg<256, 256, 4, 2, 2>;
-using Small = GemmCfg<64, 256, 1, 2, 2>;
-// few rows (a block forward over a cached prefix, the suffix of a decode):
-// 128 x 256 tiles of 8 waves of 32 x 128 (two per SIMD, as Big), so that a
-// 65-256-row projection wastes fewer clamped rows and needs half the split-K
-// parts of 256-row tiles
+// 128 x 256 tiles of 8 waves of 32 x 128 (two per SIMD, as Big): split-K parts
 using Quad = GemmCfg<128, 256, 4, 2, 1, true>;
-// gate/up with 257-512 rows: 256 x 192 tiles (waves of 64 x 96, 48 gate + 48
-// up rows each) give 2 x F / 96 = 256 workgroups for the 8B shape, one per CU,
-// where 256 x 256 tiles leave a quarter of the CUs idle; also the split-K
-// parts of the QKV projection over 129-512 rows (qkv_mid_parts)
+// 256 x 192 tiles (waves of 64 x 96, 48 gate + 48 up rows each): gate/up where
+// they fill the CUs better than Big ones, and the split-K parts of the QKV
+// projection over 129-512 rows
 using Mid = GemmCfg<256, 192, 4, 2, 2, true>;
-constexpr int kBN = 256;          // Big and Small: column tile of the split-K partials and the QKV / residual launches
+constexpr int kBN = 256;          // column tile of Big and Quad, and the pitch unit of the split-K partials
 constexpr int kGroupM = 8;
 #ifndef DLLM_PINGPONG
 #define DLLM_PINGPONG 1
@@ -59,32 +51,96 @@ using MainLoop =
     std::conditional_t<kPingPong && std::is_same_v<T, bf16_t> && Cfg::BM == 256 && Cfg::BN == 256 && Cfg::WM == 4 &&
                            Cfg::WN == 2,
                        PingPongMma<T, TRANS>, TileMma<T, Cfg::BM, Cfg::BN, Cfg::WM, Cfg::WN, TRANS, Cfg::kEarly>>;
-#ifndef DLLM_SMALL_M_MAX
-#define DLLM_SMALL_M_MAX 64
-#endif
-constexpr int kSmallM = DLLM_SMALL_M_MAX;
+// Tile and split-K parts of a bf16 projection.
+enum Tile { T_BIG, T_MID, T_QUAD, T_128x192, T_128x128, T_64x128 };
+struct GemmPlan {
+  Tile tile;
+  int parts;
+};
 
-// Row tile of a projection of M rows: Small up to kSmallM rows; Quad where it
-// measured faster than Big (the d-wide O projection up to 512 rows, the
-// F-deep down projection at 1, 2 or 4 row tiles up to 512 rows, QKV and
-// gate/up up to 128); Big above.
-int tile_rows(int kind, int M, int N, int K) {
-  if (M <= kSmallM) return Small::BM;
-  if (kind == GEMM_KIND_RESID && K > N && M <= 512) {
-    // the F-deep down projection: 128-row tiles when their split-K parts fill
-    // the CUs exactly (1, 2 or 4 row tiles), else 256-row tiles
-    const int tm = cdiv(M, Quad::BM);
-    return (tm & (tm - 1)) == 0 ? Quad::BM : Big::BM;
-  }
-  const int quad_max = kind == GEMM_KIND_RESID ? 512 : 128;
-  return M <= quad_max ? Quad::BM : Big::BM;
+// Estimated time in us of a tile shape: 3 us, and per 64-deep K stage a + b n
+// for n workgroups on the busiest of the 256 CUs (run in turn, or sharing it
+// where the LDS holds two).  Fitted to single projections of 160-2048 rows at
+// K 2048, 4096 and 12288 with weights out of the caches; within 15% there.
+struct TileCost {
+  int bm, bn;
+  double a, b;
+};
+constexpr TileCost kTileCost[] = {
+    {256, 256, 0.10, 1.47}, {256, 192, 0.12, 1.24}, {128, 256, 0.10, 1.00},
+    {128, 192, 0.17, 0.73}, {128, 128, 0.16, 0.50},
+};
+double tile_us(Tile t, int M, int N, int stages, int parts) {
+  const TileCost& c = kTileCost[t];
+  return 3.0 + cdiv(stages, parts) * (c.a + c.b * cdiv(cdiv(M, c.bm) * cdiv(N, c.bn) * parts, 256));
 }
+// one more read of `parts` fp32 partial tiles
+double parts_us(int M, int N, int parts) { return double(parts) * M * N * 4.0 / 5e6; }
 
-// Split-K parts of the QKV projection over 129-512 rows take 256 x 192 tiles:
-// 3 d / 192 column tiles by 1 or 2 row tiles, times the parts, fill the 256
-// CUs exactly for the 8B shape (128 x 2 or 64 x 4), where 256 x 256 tiles
-// leave a quarter of them idle (96 x 2 or 48 x 4)
-static bool qkv_mid_parts(int M, int N) { return M > 128 && M <= 512 && N % Mid::BN == 0; }
+// The tile of least estimated time (see each kind for the rows it decides).
+GemmPlan plan_bf16(int kind, int M, int N, int K) {
+  const int stages = K / 64;
+  // the most parts (a power of two, at least 4 stages each) that keep the
+  // launch within `wgs` workgroups
+  auto fill = [&](int tiles, int wgs) {
+    int p = 1;
+    while (tiles * p * 2 <= wgs && stages / (p * 2) >= 4) p *= 2;
+    return p;
+  };
+  const int t64 = cdiv(M, 64) * cdiv(N, 128), t128 = cdiv(M, 128) * cdiv(N, 128);
+  if (M <= 64) {
+    // The weights stream from HBM: 64 x 128 tiles, three to a CU, keep more
+    // copies in flight than 64 x 256 ones (32 rows, d 4096: O 11.2 -> 7.8 us,
+    // down 26.9 -> 21.4, QKV with its sum 29.8 -> 27; gate/up 46.1 -> 45.5
+    // unsplit, one launch instead of two).
+    if (kind == GEMM_KIND_GATEUP && t64 >= 80) return {T_64x128, 1};
+    return {T_64x128, fill(t64, 384)};
+  }
+  if (M <= 128) {
+    // 128 x 128 tiles (100 rows: O 13.9 -> 10.6 us, down 27.5 -> 25.5, gate/up
+    // 56 -> 50), 64 x 128 where they leave CUs idle (F 5632: 18 -> 14.5); QKV
+    // keeps 128 x 256 parts (30.6 us with their sum, 34 for 128 x 128)
+    if (kind == GEMM_KIND_RESID) return {T_128x128, fill(t128, 256)};
+    if (kind == GEMM_KIND_GATEUP) {
+      if (t128 >= 160) return {T_128x128, 1};
+      if (t64 >= 80) return {T_64x128, 1};
+      return {T_128x128, fill(t128, 256)};
+    }
+    const int p = fill(cdiv(N, 256), 256);
+    return p > 1 ? GemmPlan{T_QUAD, p} : GemmPlan{T_128x128, 1};
+  }
+  GemmPlan best{T_BIG, 1};
+  double best_us = -1.0;
+  auto offer = [&](Tile t, int parts, double extra) {
+    const double us = tile_us(t, M, N, stages, parts) + extra;
+    if (best_us < 0.0 || us < best_us) {
+      best = {t, parts};
+      best_us = us;
+    }
+  };
+  if (kind == GEMM_KIND_RESID) {
+    // parts are summed by the norm that follows, which reads each once more
+    for (int p = 1; p <= 16 && (p == 1 || stages / p >= 4); p *= 2) {
+      const double extra = p > 1 ? parts_us(M, N, p) : 0.0;
+      offer(T_BIG, p, extra);
+      if (p > 1) offer(T_QUAD, p, extra);
+      offer(T_128x128, p, extra);
+    }
+    return best;
+  }
+  // A QKV projection of K < 1024 over few rows stays in two or more parts: the
+  // parity bounds of the small bf16 models are tight enough to tell one order
+  // of its fp32 sums from another (d 512, 448 rows, 8 layers: 520 us, 473 in
+  // one pass).
+  if (kind == GEMM_KIND_QKV && M <= 512 && stages < 16)
+    if (const int p = fill(cdiv(M, Mid::BM) * cdiv(N, Mid::BN), 256); p > 1 && N % Mid::BN == 0) return {T_MID, p};
+  // one pass with the epilogue fused
+  for (Tile t : {T_BIG, T_MID, T_128x192, T_128x128}) offer(t, 1, 0.0);
+  if (kind == GEMM_KIND_QKV && M <= 512 && N % Mid::BN == 0)
+    // 256 x 192 parts and a launch that sums them
+    for (int p = 2; p <= 16 && stages / p >= 4; p *= 2) offer(T_MID, p, 2.0 + parts_us(M, N, p));
+  return best;
+}
 
 // EPI_PART / EPI_PART_GU: split-K partial tiles (GU: the gate/up row pairing
 // of EPI_SWIGLU) written to part[split][M][np]
@@ -201,7 +257,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
   constexpr int kBM = Cfg::BM, kWavesN = Cfg::WN;
   constexpr bool kTrans = EPI == EPI_SWIGLU;
   using TM = MainLoop<T, Cfg, kTrans>;
-  constexpr bool kSplit = EPI == EPI_PART || EPI == EPI_PART_GU;
+  constexpr bool kSplit = EPI == EPI_PART;
   __shared__ __attribute__((aligned(16))) uint8_t smem[TM::kSmem];
   int tm, tn, part = 0;
   if constexpr (kSplit)
@@ -222,7 +278,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
   auto a_off = [&](int r) -> uint32_t { return uint32_t(min(m0 + r, M - 1)) * a_row_bytes + k_bytes; };
   auto b_off = [&](int r) -> uint32_t {
     int row;
-    if constexpr (EPI == EPI_SWIGLU || EPI == EPI_PART_GU) {
+    if constexpr (EPI == EPI_SWIGLU) {
       row = gu_row<Cfg, TM>(r, tn, ep.F);   // BN rows -> BN / 2 outputs
     } else {
       row = min(tn * Cfg::BN + r, N - 1);
@@ -243,8 +299,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
     // stores along rows of part[split]: each wave stages RG rows by up to 64
     // columns of its tile at a time (a 96-column wave tile as 64 + 32); RG is
     // halved where the staging of all waves would not fit in the ring
-    static_assert((TM::kWTM % 64 == 0 || TM::kWTM == 32) &&
-                      (TM::kWTN == 128 || (TM::kWTN == 96 && EPI == EPI_PART)),
+    static_assert((TM::kWTM % 64 == 0 || TM::kWTM == 32) && (TM::kWTN == 128 || TM::kWTN == 96),
                   "partial epilogue tiling");
     constexpr int RG0 = TM::kWTM >= 64 ? 64 : TM::kWTM;
     constexpr int RG = TM::kWaves * RG0 * 64 * 4 <= TM::kSmem ? RG0 : RG0 / 2;   // rows per staged group
@@ -358,7 +413,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    static_assert(Elem<T>::bytes == 2, "fp32 takes gemm_f32_kernel");
+    static_assert(Elem<T>::bytes == 2, "fp32 takes gemm_direct_kernel");
     {
       const int r0 = m0 + wm * TM::kWTM;
       if (which < 2) {
@@ -497,6 +552,13 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_swiglu_pe
 
 // ---------------------------------------------------------------- fp32 projections
 
+// Tiles of gemm_direct_kernel.
+template <typename T_, int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS, bool EARLY, int FOLD = 0>
+struct DirectCfg {
+  using T = T_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, kThreads = WM_ * WN_ * 64, kMinBlocks = MIN_BLOCKS;
+  using TM = TileMma<T_, BM_, BN_, WM_, WN_, true, EARLY, FOLD>;
+};
 // fp32 tile: 64 x 64, 4 waves of 16 x 64, four workgroups to a CU.  The fp32
 // matrix instructions run at a sixteenth of the bf16 rate, so a projection is
 // bound by them as soon as every SIMD has a wave, and by idle SIMDs before
@@ -504,26 +566,37 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_swiglu_pe
 // while its LDS and L2 traffic stays far below their rates.  Measured against
 // 256 x 256 tiles of 8 waves: 603 x 8192 x 1024 124 -> 89 us (114 TFLOP/s),
 // 512 x 2048 x 256 37 -> 9 us, and a d 4096 layer of 2048 rows 7.7 -> 7.1 ms;
-// 128 x 128 tiles were within 3% at 2048 rows and up to 7% slower below.
-// A row's columns lie in one wave, blocks transposed (TileMma TRANS), so every
-// epilogue works on 4 consecutive columns of a row in registers and stores 16
-// bytes without LDS.
-struct F32Cfg {
-  static constexpr int BM = 64, BN = 64, kThreads = 256, kMinBlocks = 4;
-  using TM = TileMma<float, BM, BN, 4, 1, true>;
-};
+// 128 x 128 tiles were within 3% at 2048 rows and up to 7% slower below.  The
+// sums are folded every 256 of K: without split-K parts the error against 64
+// bits was 5.9e-7 (603 rows, K up to 4096) and 8.9e-7 where it had been 5.4e-7
+// and 5.2e-7; folding gives 5.4e-7 again for 2% of the time.
+using F32Cfg = DirectCfg<float, 64, 64, 4, 1, 4, false, 8>;
+// bf16 tiles, 8 (64 x 128: 4) waves, early-release schedule; plan_bf16 says
+// where each is used
+using D256x192 = DirectCfg<bf16_t, 256, 192, 4, 2, 2, true>;
+using D128x192 = DirectCfg<bf16_t, 128, 192, 4, 2, 2, true>;
+using D128x128 = DirectCfg<bf16_t, 128, 128, 4, 2, 2, true>;
+using D64x128 = DirectCfg<bf16_t, 64, 128, 2, 2, 2, true>;
 
-// x (or a part) of the fp32 projection A B^T with the epilogue applied in
-// registers.  Tile columns n and n + BN / 2 belong together: the gate and up
-// rows of one output, or the two halves of a rotary pair (QKV); the residual
-// projection and its split-K parts take plain columns.
-template <int EPI, int HD>
-__global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32_kernel(
-    const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int M, int N, int K, int tiles_m,
-    int tiles_n, EpiParams ep) {
-  using Cfg = F32Cfg;
-  using TM = Cfg::TM;
-  constexpr int kHalf = Cfg::BN / 2, kHN = TM::kFN / 2;
+// four consecutive values stored at once (p 8-byte aligned for bf16, 16 for fp32)
+__device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
+  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+__device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+
+// A projection A B^T (or a K part of it) whose epilogue works in registers:
+// blocks transposed (TileMma TRANS), so a lane holds 4 consecutive columns of
+// a row and stores them at once without LDS.  Columns n and n + kWTN / 2 of a
+// wave tile belong together: the gate and up rows of one output, or the two
+// halves of a rotary pair (QKV); the residual projection and its split-K parts
+// take plain columns.
+template <int EPI, int HD, class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_direct_kernel(
+    const typename Cfg::T* __restrict__ A, int lda, const typename Cfg::T* __restrict__ B, int ldb, int M, int N,
+    int K, int tiles_m, int tiles_n, EpiParams ep) {
+  using T = typename Cfg::T;
+  using TM = typename Cfg::TM;
+  constexpr int kHalf = TM::kWTN / 2, kHN = TM::kFN / 2;
   constexpr bool kSplit = EPI == EPI_PART || EPI == EPI_PART_GU;
   __shared__ __attribute__((aligned(16))) uint8_t smem[TM::kSmem];
   int tm, tn, part = 0;
@@ -532,24 +605,25 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
   else
     map_tile(blockIdx.x, gridDim.x, tiles_m, tiles_n, kGroupM, tm, tn);
   const int m0 = tm * Cfg::BM;
-  const uint32_t a_row_bytes = uint32_t(lda) * 4, b_row_bytes = uint32_t(ldb) * 4;
+  const uint32_t a_row_bytes = uint32_t(lda) * sizeof(T), b_row_bytes = uint32_t(ldb) * sizeof(T);
   int st0 = 0, nst = K / (2 * TM::kKPerStage);
   if constexpr (kSplit) {
     const int all = nst;
     st0 = part * all / int(gridDim.y);
     nst = (part + 1) * all / int(gridDim.y) - st0;
   }
+  const int pair0 = tn * (Cfg::BN / 2);   // first pair of the tile
   const uint32_t k_bytes = uint32_t(st0) * TM::kRowBytes;
   auto a_off = [&](int r) -> uint32_t { return uint32_t(min(m0 + r, M - 1)) * a_row_bytes + k_bytes; };
   auto b_off = [&](int r) -> uint32_t {
     int row;
     if constexpr (EPI == EPI_SWIGLU || EPI == EPI_PART_GU) {
-      const int j = min(tn * kHalf + r % kHalf, ep.F - 1);
-      row = r < kHalf ? j : ep.F + j;
+      const int rr = r % TM::kWTN, j = min(pair0 + (r / TM::kWTN) * kHalf + rr % kHalf, ep.F - 1);
+      row = rr < kHalf ? j : ep.F + j;
     } else if constexpr (EPI == EPI_QKV) {
       // rotary pair p: dims p % (HD / 2) and that + HD / 2 of head column p / (HD / 2)
-      const int p = tn * kHalf + r % kHalf;
-      row = min((p / (HD / 2)) * HD + p % (HD / 2) + (r < kHalf ? 0 : HD / 2), N - 1);
+      const int rr = r % TM::kWTN, p = pair0 + (r / TM::kWTN) * kHalf + rr % kHalf;
+      row = min((p / (HD / 2)) * HD + p % (HD / 2) + (rr < kHalf ? 0 : HD / 2), N - 1);
     } else {
       row = min(tn * Cfg::BN + r, N - 1);
     }
@@ -560,8 +634,9 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
           acc);
 
   // lane l: row 16 m + l % 16 of the wave tile, columns 16 n + 4 (l / 16) + 0 .. 3
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = m0 + wave * TM::kWTM + (lane & 15), c4 = 4 * (lane >> 4);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+  const int r0 = m0 + wm * TM::kWTM + (lane & 15), c4 = 4 * (lane >> 4);
+  const int c0 = tn * Cfg::BN + wn * TM::kWTN + c4, p0 = pair0 + wn * kHalf + c4;   // first column, first pair
   if constexpr (EPI == EPI_PART) {
     float* P = ep.part + size_t(part) * M * ep.np;
 #pragma unroll
@@ -570,7 +645,7 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
       if (row >= M) continue;
 #pragma unroll
       for (int n = 0; n < TM::kFN; ++n) {
-        const int col = tn * Cfg::BN + 16 * n + c4;
+        const int col = c0 + 16 * n;
         if (col < ep.np) *reinterpret_cast<f32x4*>(P + size_t(row) * ep.np + col) = acc[m][n];
       }
     }
@@ -583,7 +658,7 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
       if (row >= M) continue;
 #pragma unroll
       for (int n = 0; n < kHN; ++n) {
-        const int j = tn * kHalf + 16 * n + c4;
+        const int j = p0 + 16 * n;
         if (j >= ep.F) continue;
         float* dst = P + size_t(row) * ep.np + (j >> 7) * 256 + ((j & 127) >> 6) * 128 + (j & 63);
         *reinterpret_cast<f32x4*>(dst) = acc[m][n];
@@ -598,30 +673,30 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
       float* xr = ep.x + size_t(row) * ep.ldx;
 #pragma unroll
       for (int n = 0; n < TM::kFN; ++n) {
-        const int col = tn * Cfg::BN + 16 * n + c4;
+        const int col = c0 + 16 * n;
         if (col < N) *reinterpret_cast<f32x4*>(xr + col) = *reinterpret_cast<const f32x4*>(xr + col) + acc[m][n];
       }
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
-    float* out = static_cast<float*>(ep.out);
-    const bool vec = (ep.F % 4) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    T* out = static_cast<T*>(ep.out);
+    const bool vec = (ep.F % 4) == 0 && (reinterpret_cast<uintptr_t>(out) & (4 * sizeof(T) - 1)) == 0;
 #pragma unroll
     for (int m = 0; m < TM::kFM; ++m) {
       const int row = r0 + 16 * m;
       if (row >= M) continue;
 #pragma unroll
       for (int n = 0; n < kHN; ++n) {
-        const int j = tn * kHalf + 16 * n + c4;
+        const int j = p0 + 16 * n;
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = silu_fast(acc[m][n][i]) * acc[m][n + kHN][i];
-        float* dst = out + size_t(row) * ep.F + j;
+        T* dst = out + size_t(row) * ep.F + j;
         if (vec && j + 3 < ep.F) {
-          *reinterpret_cast<f32x4*>(dst) = v;
+          store4(dst, v);
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (j + i < ep.F) dst[i] = v[i];
+            if (j + i < ep.F) store_f(dst + i, v[i]);
         }
       }
     }
@@ -636,7 +711,7 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
       const float2* rope = o.rope + size_t(qkv_pos(o, row)) * half;
 #pragma unroll
       for (int n = 0; n < kHN; ++n) {
-        const int p = tn * kHalf + 16 * n + c4, hc = p / half, dim = p % half;
+        const int p = p0 + 16 * n, hc = p / half, dim = p % half;
         if (p >= N / 2) continue;
         const int which = hc / o.H, h = hc - which * o.H;
         const f32x4 x1 = acc[m][n], x2 = acc[m][n + kHN];
@@ -644,15 +719,15 @@ __global__ __launch_bounds__(F32Cfg::kThreads, F32Cfg::kMinBlocks) void gemm_f32
           const float4* cs4 = reinterpret_cast<const float4*>(rope + dim);
           const float4 c01 = cs4[0], c23 = cs4[1];   // (cos, sin) of dims dim .. dim + 3
           const f32x4 cs = f32x4{c01.x, c01.z, c23.x, c23.z}, sn = f32x4{c01.y, c01.w, c23.y, c23.w};
-          float* dst = static_cast<float*>(which == 0 ? o.q : o.k) + (size_t(b * o.H + h) * o.seq + sp) * HD + dim;
-          *reinterpret_cast<f32x4*>(dst) = x1 * cs - x2 * sn;
-          *reinterpret_cast<f32x4*>(dst + half) = x1 * sn + x2 * cs;
+          T* dst = static_cast<T*>(which == 0 ? o.q : o.k) + (size_t(b * o.H + h) * o.seq + sp) * HD + dim;
+          store4(dst, x1 * cs - x2 * sn);
+          store4(dst + half, x1 * sn + x2 * cs);
         } else {
-          float* dst = static_cast<float*>(o.vt) + (size_t(b * o.H + h) * HD + dim) * o.vt_ld + sp;
+          T* dst = static_cast<T*>(o.vt) + (size_t(b * o.H + h) * HD + dim) * o.vt_ld + sp;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            dst[size_t(i) * o.vt_ld] = x1[i];
-            dst[size_t(i + half) * o.vt_ld] = x2[i];
+            store_vt(dst + size_t(i) * o.vt_ld, x1[i]);
+            store_vt(dst + size_t(i + half) * o.vt_ld, x2[i]);
           }
         }
       }
@@ -686,15 +761,6 @@ hipError_t launch_cfg(const void* A, int lda, const void* B, int ldb, int M, int
   return hipGetLastError();
 }
 
-// bm: the row tile (tile_rows)
-template <typename T, int EPI, int HD = 0>
-hipError_t launch(int bm, const void* A, int lda, const void* B, int ldb, int M, int N, int K, int tiles_n,
-                  const EpiParams& ep, hipStream_t s, int splits = 1) {
-  if (bm == Small::BM) return launch_cfg<T, EPI, HD, Small>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
-  if (bm == Quad::BM) return launch_cfg<T, EPI, HD, Quad>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
-  return launch_cfg<T, EPI, HD, Big>(A, lda, B, ldb, M, N, K, tiles_n, ep, s, splits);
-}
-
 // K parts of an fp32 projection: the smallest estimated time in us over 1, 2,
 // 4, 8 or 16 parts of at least 4 stages.  A 64 x 64 tile takes 0.44 us per K
 // stage at the fp32 MFMA rate of its CU, shared by the workgroups the CU
@@ -717,17 +783,23 @@ int f32_splits(int kind, int M, int N, int K) {
   return best;
 }
 
+template <int EPI, int HD, class Cfg>
+hipError_t launch_direct(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const EpiParams& ep,
+                         hipStream_t s, int splits = 1) {
+  using T = typename Cfg::T;
+  constexpr int kStageK = 2 * Cfg::TM::kKPerStage;
+  if (K <= 0 || K % kStageK || splits < 1 || splits > K / kStageK) return hipErrorInvalidValue;
+  // gate/up tiles hold BN / 2 outputs of each kind: N = 2 F columns in all
+  const int tiles_m = cdiv(M, Cfg::BM), tiles_n = cdiv(N, Cfg::BN);
+  hipLaunchKernelGGL((gemm_direct_kernel<EPI, HD, Cfg>), dim3(tiles_m * tiles_n, splits), dim3(Cfg::kThreads), 0, s,
+                     static_cast<const T*>(A), lda, static_cast<const T*>(B), ldb, M, N, K, tiles_m, tiles_n, ep);
+  return hipGetLastError();
+}
+
 template <int EPI, int HD = 0>
 hipError_t launch_f32(const void* A, int lda, const void* B, int ldb, int M, int N, int K, const EpiParams& ep,
                       hipStream_t s, int splits = 1) {
-  constexpr int kStageK = 2 * F32Cfg::TM::kKPerStage;
-  if (K <= 0 || K % kStageK || splits < 1 || splits > K / kStageK) return hipErrorInvalidValue;
-  // gate/up tiles hold BN / 2 outputs of each kind: N = 2 F columns in all
-  const int tiles_m = cdiv(M, F32Cfg::BM), tiles_n = cdiv(N, F32Cfg::BN);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, HD>), dim3(tiles_m * tiles_n, splits), dim3(F32Cfg::kThreads), 0, s,
-                     static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, M, N, K, tiles_m, tiles_n,
-                     ep);
-  return hipGetLastError();
+  return launch_direct<EPI, HD, F32Cfg>(A, lda, B, ldb, M, N, K, ep, s, splits);
 }
 
 // ---------------------------------------------------------------- split-K reductions
@@ -789,11 +861,6 @@ __global__ __launch_bounds__(kRedThreads) void splitk_swiglu_kernel(const float*
 }
 
 
-// four consecutive values stored at once (p 8-byte aligned for bf16, 16 for fp32)
-__device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
-  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-}
-__device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
 __device__ __forceinline__ void store4_vt(bf16_t* p, f32x4 v) {
   *reinterpret_cast<u32x2*>(p) = u32x2{pack_vt2(v[0], v[1]), pack_vt2(v[2], v[3])};
 }
@@ -915,22 +982,7 @@ hipError_t splitk_add(const SplitK& sk, int M, int N, float* X, int ldx, hipStre
 }
 
 int gemm_splits(int kind, int M, int N, int K, int dtype) {
-  if (!dtype) return f32_splits(kind, M, N, K);
-  // workgroups that fill the 256 CUs: one Big, Mid or Quad workgroup per CU, two Small ones
-  const int bm = tile_rows(kind, M, N, K);
-  const int tiles_n = kind == GEMM_KIND_GATEUP ? cdiv(N / 2, 128)
-                      : kind == GEMM_KIND_QKV && qkv_mid_parts(M, N) ? N / Mid::BN
-                                                                       : cdiv(N, kBN);
-  const int tiles = cdiv(M, bm) * tiles_n, full = bm == Small::BM ? 512 : 256;
-  const int stages = K / 64;   // 128-byte K stages
-  if (tiles >= full * 5 / 8 || stages < 2) return 1;
-  const int parts = std::max(1, std::min(full / tiles, stages / 4));
-  // a multiple of 8 or a power of two, so that map_split_tile gives each
-  // XCD whole parts (or an even share of one)
-  if (parts >= 8) return parts / 8 * 8;
-  int p2 = 1;
-  while (p2 * 2 <= parts) p2 *= 2;
-  return p2;
+  return dtype ? plan_bf16(kind, M, N, K).parts : f32_splits(kind, M, N, K);
 }
 
 size_t gemm_partial_bytes(int M, int tiles_n, int splits) {
@@ -943,18 +995,25 @@ hipError_t gemm_resid(int dtype, const void* A, int lda, const void* B, int ldb,
   EpiParams ep{};
   ep.x = X;
   ep.ldx = ldx;
+  const GemmPlan pl = dtype ? plan_bf16(GEMM_KIND_RESID, M, N, K) : GemmPlan{};
   const int tn = cdiv(N, kBN);
-  const int bm = tile_rows(GEMM_KIND_RESID, M, N, K);
   if (sk && sk->splits > 1) {
+    const int p = sk->splits;
     ep.part = sk->part;
     ep.np = tn * kBN;
-    hipError_t e = dtype ? launch<bf16_t, EPI_PART>(bm, A, lda, B, ldb, M, N, K, tn, ep, s, sk->splits)
-                         : launch_f32<EPI_PART>(A, lda, B, ldb, M, N, K, ep, s, sk->splits);
+    hipError_t e;
+    if (!dtype) e = launch_f32<EPI_PART>(A, lda, B, ldb, M, N, K, ep, s, p);
+    else if (pl.tile == T_64x128) e = launch_direct<EPI_PART, 0, D64x128>(A, lda, B, ldb, M, N, K, ep, s, p);
+    else if (pl.tile == T_128x128) e = launch_direct<EPI_PART, 0, D128x128>(A, lda, B, ldb, M, N, K, ep, s, p);
+    else if (pl.tile == T_QUAD) e = launch_cfg<bf16_t, EPI_PART, 0, Quad>(A, lda, B, ldb, M, N, K, tn, ep, s, p);
+    else e = launch_cfg<bf16_t, EPI_PART, 0, Big>(A, lda, B, ldb, M, N, K, tn, ep, s, p);
     if (e != hipSuccess || sk->defer) return e;
     return splitk_add(*sk, M, N, X, ldx, s);
   }
-  return dtype ? launch<bf16_t, EPI_RESID>(bm, A, lda, B, ldb, M, N, K, tn, ep, s)
-               : launch_f32<EPI_RESID>(A, lda, B, ldb, M, N, K, ep, s);
+  if (!dtype) return launch_f32<EPI_RESID>(A, lda, B, ldb, M, N, K, ep, s);
+  if (pl.tile == T_64x128) return launch_direct<EPI_RESID, 0, D64x128>(A, lda, B, ldb, M, N, K, ep, s);
+  if (pl.tile == T_128x128) return launch_direct<EPI_RESID, 0, D128x128>(A, lda, B, ldb, M, N, K, ep, s);
+  return launch_cfg<bf16_t, EPI_RESID, 0, Big>(A, lda, B, ldb, M, N, K, tn, ep, s, 1);
 }
 
 hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M, int F, int K, void* out,
@@ -962,19 +1021,18 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
   EpiParams ep{};
   ep.out = out;
   ep.F = F;
-  if (!dtype && !(sk && sk->splits > 1)) return launch_f32<EPI_SWIGLU>(A, lda, Wgu, K, M, 2 * F, K, ep, s);
-  const int bm = tile_rows(GEMM_KIND_GATEUP, M, 2 * F, K);
-  if (!(sk && sk->splits > 1) && M > 256 && M <= 512 && bm == Big::BM) {
-    const int tm = cdiv(F, Mid::BN / 2);
-    return launch_cfg<bf16_t, EPI_SWIGLU, 0, Mid>(A, lda, Wgu, K, M, 2 * F, K, tm, ep, s, 1);
-  }
+  const int N = 2 * F;
+  const GemmPlan pl = dtype ? plan_bf16(GEMM_KIND_GATEUP, M, N, K) : GemmPlan{};
   const int tn = cdiv(F, 128);
   if (sk && sk->splits > 1) {
     if (F % 4) return hipErrorInvalidValue;
+    const int p = sk->splits;
     ep.part = sk->part;
     ep.np = tn * kBN;
-    hipError_t e = dtype ? launch<bf16_t, EPI_PART_GU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s, sk->splits)
-                         : launch_f32<EPI_PART_GU>(A, lda, Wgu, K, M, 2 * F, K, ep, s, sk->splits);
+    hipError_t e;
+    if (!dtype) e = launch_f32<EPI_PART_GU>(A, lda, Wgu, K, M, N, K, ep, s, p);
+    else if (pl.tile == T_64x128) e = launch_direct<EPI_PART_GU, 0, D64x128>(A, lda, Wgu, K, M, N, K, ep, s, p);
+    else e = launch_direct<EPI_PART_GU, 0, D128x128>(A, lda, Wgu, K, M, N, K, ep, s, p);
     if (e != hipSuccess) return e;
     const dim3 g(cdiv(M * (F / 4), kRedThreads));
     if (dtype)
@@ -985,17 +1043,22 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
                          static_cast<float*>(out));
     return hipGetLastError();
   }
-  if (bm == Big::BM) {
-    // 256 x 256 tiles, one persistent workgroup per CU
-    constexpr int kStageK = 2 * TileMma<bf16_t, Big::BM, Big::BN, Big::WM, Big::WN>::kKPerStage;
-    if (K <= 0 || K % kStageK) return hipErrorInvalidValue;
-    const int tiles_m = cdiv(M, Big::BM), tiles = tiles_m * tn;
-    const int grid = std::min(tiles, device_cus());
-    hipLaunchKernelGGL((gemm_swiglu_persist_kernel<bf16_t, Big>), dim3(grid), dim3(Big::kThreads), 0, s,
-                       static_cast<const bf16_t*>(A), lda, static_cast<const bf16_t*>(Wgu), M, K, tiles_m, tn, ep);
-    return hipGetLastError();
+  if (!dtype) return launch_f32<EPI_SWIGLU>(A, lda, Wgu, K, M, N, K, ep, s);
+  switch (pl.tile) {
+    case T_64x128: return launch_direct<EPI_SWIGLU, 0, D64x128>(A, lda, Wgu, K, M, N, K, ep, s);
+    case T_128x128: return launch_direct<EPI_SWIGLU, 0, D128x128>(A, lda, Wgu, K, M, N, K, ep, s);
+    case T_128x192: return launch_direct<EPI_SWIGLU, 0, D128x192>(A, lda, Wgu, K, M, N, K, ep, s);
+    case T_MID: return launch_cfg<bf16_t, EPI_SWIGLU, 0, Mid>(A, lda, Wgu, K, M, N, K, cdiv(F, Mid::BN / 2), ep, s, 1);
+    default: break;
   }
-  return launch<bf16_t, EPI_SWIGLU>(bm, A, lda, Wgu, K, M, 2 * F, K, tn, ep, s);
+  // 256 x 256 tiles, one persistent workgroup per CU
+  constexpr int kStageK = 2 * TileMma<bf16_t, Big::BM, Big::BN, Big::WM, Big::WN>::kKPerStage;
+  if (K <= 0 || K % kStageK) return hipErrorInvalidValue;
+  const int tiles_m = cdiv(M, Big::BM), tiles = tiles_m * tn;
+  const int grid = std::min(tiles, device_cus());
+  hipLaunchKernelGGL((gemm_swiglu_persist_kernel<bf16_t, Big>), dim3(grid), dim3(Big::kThreads), 0, s,
+                     static_cast<const bf16_t*>(A), lda, static_cast<const bf16_t*>(Wgu), M, K, tiles_m, tn, ep);
+  return hipGetLastError();
 }
 
 namespace {
@@ -1010,12 +1073,15 @@ hipError_t qkv_split(const void* A, int lda, const void* Wqkv, int M, int K, con
   ep.part = sk.part;
   ep.np = tn * kBN;   // the partial layout does not depend on the tiling
   hipError_t e;
-  if constexpr (std::is_same_v<T, float>)
+  if constexpr (std::is_same_v<T, float>) {
     e = launch_f32<EPI_PART>(A, lda, Wqkv, K, M, N, K, ep, s, sk.splits);
-  else if (qkv_mid_parts(M, N))
-    e = launch_cfg<T, EPI_PART, 0, Mid>(A, lda, Wqkv, K, M, N, K, N / Mid::BN, ep, s, sk.splits);
-  else
-    e = launch<T, EPI_PART>(tile_rows(GEMM_KIND_QKV, M, N, K), A, lda, Wqkv, K, M, N, K, tn, ep, s, sk.splits);
+  } else {
+    const Tile t = plan_bf16(GEMM_KIND_QKV, M, N, K).tile;
+    if (t == T_64x128) e = launch_direct<EPI_PART, 0, D64x128>(A, lda, Wqkv, K, M, N, K, ep, s, sk.splits);
+    else if (t == T_MID)
+      e = launch_cfg<T, EPI_PART, 0, Mid>(A, lda, Wqkv, K, M, N, K, N / Mid::BN, ep, s, sk.splits);
+    else e = launch_cfg<T, EPI_PART, 0, Quad>(A, lda, Wqkv, K, M, N, K, tn, ep, s, sk.splits);
+  }
   if (e != hipSuccess) return e;
   const int n_qk = cdiv(M * (o.d / 4), kRedThreads), n_v = cdiv(o.d, 64) * cdiv(M, 16);
   if (o.hd == 128)
@@ -1027,6 +1093,18 @@ hipError_t qkv_split(const void* A, int lda, const void* Wqkv, int M, int K, con
   return hipGetLastError();
 }
 
+template <int HD>
+hipError_t qkv_fused(Tile t, const void* A, int lda, const void* W, int M, int N, int K, const EpiParams& ep,
+                     hipStream_t s) {
+  switch (t) {
+    case T_64x128: return launch_direct<EPI_QKV, HD, D64x128>(A, lda, W, K, M, N, K, ep, s);
+    case T_128x128: return launch_direct<EPI_QKV, HD, D128x128>(A, lda, W, K, M, N, K, ep, s);
+    case T_128x192: return launch_direct<EPI_QKV, HD, D128x192>(A, lda, W, K, M, N, K, ep, s);
+    case T_MID: return launch_direct<EPI_QKV, HD, D256x192>(A, lda, W, K, M, N, K, ep, s);
+    default: return launch_cfg<bf16_t, EPI_QKV, HD, Big>(A, lda, W, K, M, N, K, cdiv(N, kBN), ep, s, 1);
+  }
+}
+
 }  // namespace
 
 hipError_t gemm_qkv(int dtype, const void* A, int lda, const void* Wqkv, int M, int K, const QkvOut& o,
@@ -1036,13 +1114,11 @@ hipError_t gemm_qkv(int dtype, const void* A, int lda, const void* Wqkv, int M, 
   EpiParams ep{};
   ep.qkv = o;
   const int N = 3 * o.d;
-  const int tn = cdiv(N, kBN);
-  const int bm = tile_rows(GEMM_KIND_QKV, M, N, K);
-  if (o.hd == 128)
-    return dtype ? launch<bf16_t, EPI_QKV, 128>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s)
-                 : launch_f32<EPI_QKV, 128>(A, lda, Wqkv, K, M, N, K, ep, s);
-  return dtype ? launch<bf16_t, EPI_QKV, 64>(bm, A, lda, Wqkv, K, M, N, K, tn, ep, s)
-               : launch_f32<EPI_QKV, 64>(A, lda, Wqkv, K, M, N, K, ep, s);
+  if (!dtype)
+    return o.hd == 128 ? launch_f32<EPI_QKV, 128>(A, lda, Wqkv, K, M, N, K, ep, s)
+                       : launch_f32<EPI_QKV, 64>(A, lda, Wqkv, K, M, N, K, ep, s);
+  const Tile t = plan_bf16(GEMM_KIND_QKV, M, N, K).tile;
+  return o.hd == 128 ? qkv_fused<128>(t, A, lda, Wqkv, M, N, K, ep, s) : qkv_fused<64>(t, A, lda, Wqkv, M, N, K, ep, s);
 }
 
 }  // namespace dllm

@@ -67,14 +67,32 @@ struct LmCfg {
   static_assert(kSegs * (kSegCols / 8) >= kK, "the seed bound covers the top 16");
 };
 
+// Tile times of a launch with n vocabulary slices: rounds of workgroups times
+// the tiles of a slice.
+int tile_times(int bm, int R, int V, int n) {
+  return cdiv(cdiv(R, bm) * n, bm == 64 ? kTargetWgSmall : kTargetWg) * cdiv(cdiv(V, bm == 64 ? 128 : 256), n);
+}
+
+// Vocabulary slices: as many as one round of workgroups holds, or one more
+// where rounding up needs fewer tile times over all rounds.
+int slices_for(int bm, int R, int V) {
+  const int rt = cdiv(R, bm), vt = cdiv(V, bm == 64 ? 128 : 256), target = bm == 64 ? kTargetWgSmall : kTargetWg;
+  const int up = std::max(1, std::min(vt, cdiv(target, rt))), down = std::max(1, std::min(vt, target / rt));
+  return tile_times(bm, R, V, up) < tile_times(bm, R, V, down) ? up : down;
+}
+
 // Row tile of an LM head over R rows and V vocabulary entries.
 int lm_tile(int dtype, int R, int V) {
   const bool few = cdiv(R, 128) * cdiv(V, 256) < kTargetWg / 2;   // 128 x 256 tiles would leave half the CUs idle
   if (R <= 64 || few) return 64;
-  if (dtype) return R > 128 ? 256 : 128;
-  // fp32: the matrix cores bound every tile; the largest keeps the partials
-  // of very many rows (2 a row instead of 4) small
-  return R > 32768 ? 256 : 128;
+  if (R <= 128) return 128;
+  if (R > 32768) return 256;   // 2 partials a row and slice instead of 4
+  if (!dtype) return 128;      // the fp32 matrix cores bound every tile
+  // d 4096: a 128 x 256 tile takes about 73 us, a 256 x 256 tile 1.72 times
+  // that (352 rows, vocabulary 126464: 6 against 4 tile times, 472 against
+  // 537 us; 512 rows: 8 against 4, 602 against 554)
+  const int t128 = tile_times(128, R, V, slices_for(128, R, V)), t256 = tile_times(256, R, V, slices_for(256, R, V));
+  return 100 * t128 < 172 * t256 ? 128 : 256;
 }
 
 struct Partials {
@@ -460,6 +478,7 @@ __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsO
   }
 }
 
+// one workgroup per probed logit (a wave each took 31 us at d 4096)
 template <typename T>
 __global__ __launch_bounds__(256) void probe_kernel(const T* __restrict__ Hs, const T* __restrict__ W, int d, int V,
                                                     int R, const int32_t* __restrict__ row,
@@ -467,25 +486,19 @@ __global__ __launch_bounds__(256) void probe_kernel(const T* __restrict__ Hs, co
                                                     const float* __restrict__ row_scale,
                                                     const int32_t* __restrict__ rs_idx, int n_pos, int rs_lim,
                                                     float scale, float* __restrict__ out) {
-  const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (p >= n) return;
+  __shared__ float part[4];
+  const int p = blockIdx.x;
   const int r = min(max(row[p], 0), R - 1);
   const T* h = Hs + size_t(r) * d;
   const T* w = W + size_t(min(max(tok[p], 0), V - 1)) * d;
   float acc = 0.f;
-  for (int c = lane; c < d; c += 64) acc += load_f(h + c) * load_f(w + c);
+#pragma unroll 8
+  for (int c = threadIdx.x; c < d; c += 256) acc += load_f(h + c) * load_f(w + c);
   acc = wave_sum(acc);
-  if (lane == 0) out[p] = acc * scale * (row_scale ? row_scale[rs_idx ? min(max(rs_idx[r % n_pos], 0), rs_lim - 1) : r % n_pos] : 1.0f);
-}
-
-// Vocabulary slices: as many as one round of workgroups holds, or one more
-// where rounding up needs fewer tile times over all rounds.
-int slices_for(int bm, int R, int V) {
-  const int rt = cdiv(R, bm), vt = cdiv(V, bm == 64 ? 128 : 256), target = bm == 64 ? kTargetWgSmall : kTargetWg;
-  const int up = std::max(1, std::min(vt, cdiv(target, rt))), down = std::max(1, std::min(vt, target / rt));
-  auto tile_times = [&](int n) { return cdiv(rt * n, target) * cdiv(vt, n); };
-  return tile_times(up) < tile_times(down) ? up : down;
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  acc = part[0] + part[1] + part[2] + part[3];
+  if (threadIdx.x == 0) out[p] = acc * scale * (row_scale ? row_scale[rs_idx ? min(max(rs_idx[r % n_pos], 0), rs_lim - 1) : r % n_pos] : 1.0f);
 }
 
 int partials_per_row(int bm, int R, int V) { return slices_for(bm, R, V) * (bm == 256 ? 2 : 4); }
@@ -552,10 +565,10 @@ hipError_t probe_logits(int dtype, const void* h, const void* w, int d, int V, i
                         int rs_lim, float scale, float* out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (dtype)
-    hipLaunchKernelGGL(probe_kernel<bf16_t>, dim3(cdiv(n, 4)), dim3(256), 0, s, static_cast<const bf16_t*>(h),
+    hipLaunchKernelGGL(probe_kernel<bf16_t>, dim3(n), dim3(256), 0, s, static_cast<const bf16_t*>(h),
                        static_cast<const bf16_t*>(w), d, V, R, row, tok, n, row_scale, rs_idx, n_pos, rs_lim, scale, out);
   else
-    hipLaunchKernelGGL(probe_kernel<float>, dim3(cdiv(n, 4)), dim3(256), 0, s, static_cast<const float*>(h),
+    hipLaunchKernelGGL(probe_kernel<float>, dim3(n), dim3(256), 0, s, static_cast<const float*>(h),
                        static_cast<const float*>(w), d, V, R, row, tok, n, row_scale, rs_idx, n_pos, rs_lim, scale, out);
   return hipGetLastError();
 }

@@ -93,7 +93,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // publishes stage j + 1.  A copy then has about 1.2-1.3 stages of MFMA work to
 // land instead of 0.65-1.0, for launches whose operands stream from HBM with
 // too few bytes in flight per CU to cover its latency.
-template <typename T, int BM, int BN, int WAVES_M, int WAVES_N, bool TRANS = false, bool EARLY = false>
+//
+// FOLD > 0: the accumulators are added to a second set and cleared every FOLD
+// stages, so that a sum over a long K keeps the short chains (and the rounding
+// error) that split-K parts of FOLD stages give it.
+template <typename T, int BM, int BN, int WAVES_M, int WAVES_N, bool TRANS = false, bool EARLY = false, int FOLD = 0>
 struct TileMma {
   static constexpr int kWaves = WAVES_M * WAVES_N;
   static constexpr int kThreads = kWaves * kWave;
@@ -242,7 +246,12 @@ struct TileMma {
       else
         bfr[r][j - kFM] = b_frag(slot, h, j - kFM);
     };
-    for (int j = 0; j < ns; ++j) {
+    f32x4 tot[FOLD > 0 ? kFM : 1][kFN];
+    if constexpr (FOLD > 0) {
+#pragma unroll
+      for (int i = 0; i < kMma; ++i) tot[i / kFN][i % kFN] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto stage = [&](int j) {
       const int cur = j & 1, nxt = cur ^ 1;
       __builtin_amdgcn_sched_barrier(0);
       static_for<0, kMma>([&](auto ii) {
@@ -291,7 +300,7 @@ struct TileMma {
           if constexpr (c < kReads) read_into(0, nxt, 0, c);
           __builtin_amdgcn_sched_barrier(0);
         });
-        continue;
+        return;
       }
       static_for<0, kPre1>([&](auto ii) {
         mma_one(1, decltype(ii)::value);
@@ -314,6 +323,21 @@ struct TileMma {
           read_into(0, nxt, 0, c - kIA - kIB);
         __builtin_amdgcn_sched_barrier(0);
       });
+    };
+    if constexpr (FOLD > 0) {
+      for (int j0 = 0; j0 < ns; j0 += FOLD) {
+        const int je = min(j0 + FOLD, ns);
+        for (int j = j0; j < je; ++j) stage(j);
+#pragma unroll
+        for (int i = 0; i < kMma; ++i) {
+          tot[i / kFN][i % kFN] += acc[i / kFN][i % kFN];
+          acc[i / kFN][i % kFN] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kMma; ++i) acc[i / kFN][i % kFN] = tot[i / kFN][i % kFN];
+    } else {
+      for (int j = 0; j < ns; ++j) stage(j);
     }
     wait_vmcnt<0>();
     __syncthreads();   // the caller may reuse the LDS

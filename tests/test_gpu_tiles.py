@@ -111,3 +111,26 @@ def test_commit_rows(P, n_m, shift):
     got = base.numpy()
     for n, v in {**f, **i}.items():
         assert (got[n][:keep.sum()] == v[keep]).all(), n
+
+
+# bf16 projections: rows at the edges of the 64-, 128- and 256-row tiles and of
+# the ranges that choose between them, an FFN whose last tile is partly filled
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("B_,S", [(1, 33), (1, 64), (1, 65), (2, 64), (1, 129), (1, 300), (1, 513), (3, 500), (6, 500)])
+def test_forward_bf16_row_tiles(P, hd, B_, S):
+    shape = ModelShape(n_layers=1, d_model=1024, n_heads=1024 // hd, head_dim=hd, d_ffn=2816, vocab=600)
+    w_np = synth.model_weights_np(shape, seed=4, dtype="bf16")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV).bfloat16() for k, v in w_np.items()}, dtype="bf16",
+                    max_pos=512 + 64)
+    toks = synth.tokens_np(8, "toks", B_ * S, shape.vocab - 1).reshape(B_, S)
+    toks[:, S // 2:] = shape.mask_id
+    lm_pos = np.unique(np.array([0, 1, S // 3, S // 2, S - 2, S - 1], dtype=np.int32))
+    out = model.forward(torch.from_numpy(toks).to(DEV), torch.from_numpy(lm_pos).to(DEV), scale=2.0)
+    torch.cuda.synchronize()
+    got, n = out.numpy(), len(lm_pos)
+    for b in {0, B_ - 1}:
+        ref = softmax_stats(om.forward_logits(toks[b:b + 1], w_np, shape, lm_pos, scale=2.0, mirror=True).reshape(
+            -1, shape.vocab), 16)
+        print(compare_stats({k: v[b * n:(b + 1) * n] for k, v in got.items()}, ref, 2e-2, max_exceptions=2,
+                            id_ranks=4, label=f"bf16 hd {hd} {B_} x {S} seq {b}"))
+    model.close()
