@@ -365,7 +365,7 @@ dllm_status forward_impl(dllm_model* m, const int32_t* tokens, int32_t batch, in
   const GemmSplits gs = plan_gemms(d, Mi);
   float* part = reinterpret_cast<float*>(base + L.part);
   // the residual projections leave their partials to the RMSNorm that follows
-  const SplitK sk_qkv{part, gs.qkv}, sk_o{part, gs.o, true}, sk_gu{part, gs.gu}, sk_down{part, gs.down, true};
+  const SplitK sk_qkv{part, gs.qkv}, sk_o{part, gs.o}, sk_gu{part, gs.gu}, sk_down{part, gs.down};
   const int np_d = (dm + 255) / 256 * 256;   // partial row pitch of the d-wide projections
   int pending = 0;                            // split-K parts of x not yet added (0: none)
   // gathered row of each LM-head row (indexed modulo lm_n, per sequence) and
@@ -385,20 +385,22 @@ dllm_status forward_impl(dllm_model* m, const int32_t* tokens, int32_t batch, in
 
   {
     ProfScope ps(m, s, DLLM_PROF_EMBED);
-    TRY_HIP(embed(dt, tokens, Mi, m->emb, dm, d.vocab, x, s), "embed");
+    TRY_HIP(embed_rmsnorm(dt, tokens, Mi, m->emb, dm, d.vocab, d.rms_eps, x, a, s), "embed_rmsnorm");
   }
   // a = rmsnorm(x), first adding the pending split-K partials of the last residual projection
   auto norm_into_a = [&]() -> dllm_status {
     ProfScope ps(m, s, DLLM_PROF_RMSNORM);
     if (pending > 1)
-      TRY_HIP(resid_rmsnorm(dt, part, pending, np_d, Mi, x, dm, d.rms_eps, a, s), "resid_rmsnorm");
+      TRY_HIP(resid_rmsnorm(dt, part, pending, np_d, Mi, x, dm, d.rms_eps, Mi, nullptr, 1, seq, a, s),
+              "resid_rmsnorm");
     else
       TRY_HIP(rmsnorm(dt, x, dm, d.rms_eps, Mi, nullptr, 1, seq, a, s), "rmsnorm");
     pending = 0;
     return DLLM_OK;
   };
   for (int l = 0; l < d.n_layers; ++l) {
-    if (dllm_status e = norm_into_a(); e != DLLM_OK) return e;
+    if (l > 0)   // layer 0's comes with the embedding
+      if (dllm_status e = norm_into_a(); e != DLLM_OK) return e;
     QkvOut qo{q, k, vt, seq, L.vt_ld, pos_offset, H, hd, dm, m->rope};
     if (pk) {
       qo.pack_S = pk->S;
@@ -459,13 +461,13 @@ dllm_status forward_impl(dllm_model* m, const int32_t* tokens, int32_t batch, in
       pending = sk_down.splits;
     }
   }
-  if (pending > 1) {
-    ProfScope ps(m, s, DLLM_PROF_GEMM_DOWN);
-    TRY_HIP(splitk_add(sk_down, Mi, dm, x, dm, s), "split-K residual");
-  }
   {
     ProfScope ps(m, s, DLLM_PROF_RMSNORM);
-    TRY_HIP(rmsnorm(dt, x, dm, d.rms_eps, R, lm_row, lm_n, seq, hl, s), "final rmsnorm");
+    if (pending > 1)
+      TRY_HIP(resid_rmsnorm(dt, part, pending, np_d, Mi, x, dm, d.rms_eps, R, lm_row, lm_n, seq, hl, s),
+              "final resid_rmsnorm");
+    else
+      TRY_HIP(rmsnorm(dt, x, dm, d.rms_eps, R, lm_row, lm_n, seq, hl, s), "final rmsnorm");
   }
   {
     ProfScope ps(m, s, DLLM_PROF_LMHEAD);

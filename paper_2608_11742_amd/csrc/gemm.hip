@@ -806,28 +806,6 @@ hipError_t launch_f32(const void* A, int lda, const void* B, int ldb, int M, int
 
 constexpr int kRedThreads = 256;
 
-// x[row][c..c+3] += part[0] + part[1] + ... (in this order)
-__global__ __launch_bounds__(kRedThreads) void splitk_resid_kernel(const float* __restrict__ part, int splits,
-                                                                   int M, int N, int np, float* __restrict__ x,
-                                                                   int ldx) {
-  const int n4 = N >> 2;
-  const int i = blockIdx.x * kRedThreads + threadIdx.x;
-  if (i >= M * n4) return;
-  const int row = i / n4, c = (i - row * n4) * 4;
-  f32x4 acc = *reinterpret_cast<const f32x4*>(x + size_t(row) * ldx + c);
-  auto pr = [&](int p) { return *reinterpret_cast<const f32x4*>(part + (size_t(p) * M + row) * np + c); };
-  int p = 0;
-  for (; p + 8 <= splits; p += 8) {   // eight loads in flight, added in order
-    f32x4 a[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = pr(p + q);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc += a[q];
-  }
-  for (; p < splits; ++p) acc += pr(p);
-  *reinterpret_cast<f32x4*>(x + size_t(row) * ldx + c) = acc;
-}
-
 // out[row][j..j+3] = silu(g) * u; gate j sits at partial column
 // (j / 128) * 256 + ((j % 128) / 64) * 128 + j % 64, its up partner 64 further
 template <typename T>
@@ -974,13 +952,6 @@ __global__ __launch_bounds__(kRedThreads) void splitk_qkv_kernel(const float* __
 
 }  // namespace
 
-hipError_t splitk_add(const SplitK& sk, int M, int N, float* X, int ldx, hipStream_t s) {
-  if (N % 4 || ldx % 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(splitk_resid_kernel, dim3(cdiv(M * (N / 4), kRedThreads)), dim3(kRedThreads), 0, s, sk.part,
-                     sk.splits, M, N, cdiv(N, kBN) * kBN, X, ldx);
-  return hipGetLastError();
-}
-
 int gemm_splits(int kind, int M, int N, int K, int dtype) {
   return dtype ? plan_bf16(kind, M, N, K).parts : f32_splits(kind, M, N, K);
 }
@@ -1007,8 +978,7 @@ hipError_t gemm_resid(int dtype, const void* A, int lda, const void* B, int ldb,
     else if (pl.tile == T_128x128) e = launch_direct<EPI_PART, 0, D128x128>(A, lda, B, ldb, M, N, K, ep, s, p);
     else if (pl.tile == T_QUAD) e = launch_cfg<bf16_t, EPI_PART, 0, Quad>(A, lda, B, ldb, M, N, K, tn, ep, s, p);
     else e = launch_cfg<bf16_t, EPI_PART, 0, Big>(A, lda, B, ldb, M, N, K, tn, ep, s, p);
-    if (e != hipSuccess || sk->defer) return e;
-    return splitk_add(*sk, M, N, X, ldx, s);
+    return e;
   }
   if (!dtype) return launch_f32<EPI_RESID>(A, lda, B, ldb, M, N, K, ep, s);
   if (pl.tile == T_64x128) return launch_direct<EPI_RESID, 0, D64x128>(A, lda, B, ldb, M, N, K, ep, s);

@@ -24,11 +24,11 @@ struct QkvOut {
 
 // Split-K of a projection GEMM with few rows: `splits` parts of the K range
 // write fp32 partial tiles to `part` (gemm_partial_bytes), reduced in a fixed
-// order by a second kernel that applies the epilogue.  splits <= 1: one pass.
+// order by a second kernel that applies the epilogue (gemm_resid: the norm
+// that follows, resid_rmsnorm).  splits <= 1: one pass.
 struct SplitK {
   float* part;
   int splits;
-  bool defer = false;   // resid: write the partials only; the caller adds them (resid_rmsnorm / splitk_add)
 };
 // split-K parts of a projection of M rows, N outputs (gate/up: 2 F, the
 // gate and up rows) and depth K
@@ -36,7 +36,8 @@ enum { GEMM_KIND_QKV = 0, GEMM_KIND_RESID = 1, GEMM_KIND_GATEUP = 2 };
 int gemm_splits(int kind, int M, int N, int K, int dtype);
 size_t gemm_partial_bytes(int M, int tiles_n, int splits);
 
-// X[M][N] (fp32, row stride ldx) += A[M][K] B[N][K]^T
+// X[M][N] (fp32, row stride ldx) += A[M][K] B[N][K]^T; with splits > 1 the
+// parts are written and X is left to resid_rmsnorm
 hipError_t gemm_resid(int dtype, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* X,
                       int ldx, hipStream_t s, const SplitK* sk = nullptr);
 // out[M][F] = silu(A Wg^T) * (A Wu^T) with Wgu = [Wg; Wu] ([2F][K])
@@ -46,15 +47,15 @@ hipError_t gemm_swiglu(int dtype, const void* A, int lda, const void* Wgu, int M
 hipError_t gemm_qkv(int dtype, const void* A, int lda, const void* Wqkv, int M, int K, const QkvOut& o,
                     hipStream_t s, const SplitK* sk = nullptr);
 
-// x[M][N] += the deferred split-K partials of gemm_resid (fixed order)
-hipError_t splitk_add(const SplitK& sk, int M, int N, float* X, int ldx, hipStream_t s);
-// x[r] += the deferred split-K partials of gemm_resid (row pitch np), then
-// out[r] = rmsnorm(x[r]), for rows 0 .. M-1
+// x[r] += the deferred split-K partials of gemm_resid (row pitch np, M rows),
+// then out[r] = rmsnorm(x[r]), for rows 0 .. rows-1.  With pos the rows are
+// gathered as in rmsnorm below and x is left as it was.
 hipError_t resid_rmsnorm(int dtype, const float* part, int splits, int np, int M, float* x, int d, float eps,
-                         void* out, hipStream_t s);
+                         int rows, const int32_t* pos, int n_pos, int seq, void* out, hipStream_t s);
 
-// x[r][:] = emb[tok[r]][:] as fp32
-hipError_t embed(int dtype, const int32_t* tok, int rows, const void* emb, int d, int vocab, float* x, hipStream_t s);
+// x[r][:] = emb[tok[r]][:] as fp32, out[r] = rmsnorm(x[r])
+hipError_t embed_rmsnorm(int dtype, const int32_t* tok, int rows, const void* emb, int d, int vocab, float eps,
+                         float* x, void* out, hipStream_t s);
 // out[r] = x[src(r)] / sqrt(mean(x^2) + eps); src(r) = r, or b * seq + pos[j] for
 // r = b * n_pos + j when pos is given
 hipError_t rmsnorm(int dtype, const float* x, int d, float eps, int rows, const int32_t* pos, int n_pos, int seq,

@@ -1,5 +1,5 @@
-// Row-wise kernels of the forward: embedding gather, RMSNorm (optionally
-// gathering rows) and the prefix-cache writer.
+// Row-wise kernels of the forward: embedding gather with the first RMSNorm,
+// RMSNorm (optionally gathering rows) and the prefix-cache writer.
 #include "kernels.h"
 #include "common.h"
 
@@ -8,16 +8,6 @@ namespace dllm {
 namespace {
 
 constexpr int kRowThreads = 256;
-
-template <typename T>
-__global__ __launch_bounds__(kRowThreads) void embed_kernel(const int32_t* __restrict__ tok, const T* __restrict__ emb,
-                                                            int d, int vocab, float* __restrict__ x) {
-  const int r = blockIdx.x;
-  const int t = min(max(tok[r], 0), vocab - 1);
-  const T* src = emb + size_t(t) * d;
-  float* dst = x + size_t(r) * d;
-  for (int c = threadIdx.x; c < d; c += kRowThreads) dst[c] = load_f(src + c);
-}
 
 // store 4 consecutive values as one 8-byte (bf16) or 16-byte (fp32) access
 __device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
@@ -64,19 +54,68 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_kernel(const float* __res
   }
 }
 
+// Embedding and the first layer's RMSNorm of one row: x[r] = emb[tok[r]],
+// out[r] = x[r] / sqrt(mean(x[r]^2) + eps).  Two launches of 11 and 5 us for
+// 512 rows of 4096 (2-byte loads) before.
+template <typename T>
+__global__ __launch_bounds__(kRowThreads) void embed_rmsnorm_kernel(const int32_t* __restrict__ tok,
+                                                                    const T* __restrict__ emb, int d, int vocab,
+                                                                    float eps, float* __restrict__ x,
+                                                                    T* __restrict__ out, bool wide) {
+  __shared__ float part[kRowThreads / kWave];
+  const int r = blockIdx.x;
+  const T* src = emb + size_t(min(max(tok[r], 0), vocab - 1)) * d;
+  f32x4 v[kNormChunks];
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < kNormChunks; ++j) {
+    const int c = (threadIdx.x + j * kRowThreads) * 4;
+    v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (c < d) {
+      if (!wide) {   // an embedding that starts off a 16-byte boundary
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = load_f(src + c + e);
+      } else if constexpr (Elem<T>::bytes == 2) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(src + c);
+        v[j] = f32x4{bf2f(uint16_t(w.x)), bf2f(uint16_t(w.x >> 16)), bf2f(uint16_t(w.y)), bf2f(uint16_t(w.y >> 16))};
+      } else {
+        v[j] = *reinterpret_cast<const f32x4*>(src + c);
+      }
+      *reinterpret_cast<f32x4*>(x + size_t(r) * d + c) = v[j];
+    }
+    ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < kRowThreads / kWave; ++w) tot += part[w];
+  const float inv = 1.0f / sqrtf(tot / float(d) + eps);
+#pragma unroll
+  for (int j = 0; j < kNormChunks; ++j) {
+    const int c = (threadIdx.x + j * kRowThreads) * 4;
+    if (c < d) store4(out + size_t(r) * d + c, v[j] * inv);
+  }
+}
+
 // Residual update from split-K partial tiles fused with the RMSNorm that
-// follows it: x[r] += part[0][r] + part[1][r] + ... (in this order, as the
-// separate reduction), then out[r] = x[r] / sqrt(mean(x[r]^2) + eps).
+// follows it: x[r] += part[0][r] + part[1][r] + ... (in this order), then
+// out[r] = x[r] / sqrt(mean(x[r]^2) + eps).  With pos (the final norm): output
+// row r reads row src(r) as in rmsnorm_kernel, and x, which nothing reads
+// after it, is not written back.
 template <typename T, int THREADS>
 __global__ __launch_bounds__(THREADS) void resid_rmsnorm_kernel(const float* __restrict__ part, int splits, int np,
                                                                 int M, float* __restrict__ x, int d, float eps,
+                                                                const int32_t* __restrict__ pos, int n_pos, int seq,
                                                                 T* __restrict__ out) {
   constexpr int CH = kNormChunks * kRowThreads / THREADS;   // 16-byte chunks per thread: d <= 8192
   constexpr int LIF = CH <= 2 ? 8 : 4;                       // partial loads in flight per chunk
   __shared__ float red[THREADS / kWave];
   const int r = blockIdx.x;
-  float* xr = x + size_t(r) * d;
-  auto pr = [&](int p, int c) { return *reinterpret_cast<const f32x4*>(part + (size_t(p) * M + r) * np + c); };
+  const int sr = pos ? (r / n_pos) * seq + min(max(pos[r % n_pos], 0), seq - 1) : r;
+  float* xr = x + size_t(sr) * d;
+  auto pr = [&](int p, int c) { return *reinterpret_cast<const f32x4*>(part + (size_t(p) * M + sr) * np + c); };
   f32x4 v[CH];
   float ss = 0.f;
 #pragma unroll
@@ -94,7 +133,7 @@ __global__ __launch_bounds__(THREADS) void resid_rmsnorm_kernel(const float* __r
         for (int q = 0; q < LIF; ++q) v[j] += a[q];
       }
       for (; p < splits; ++p) v[j] += pr(p, c);
-      *reinterpret_cast<f32x4*>(xr + c) = v[j];
+      if (!pos) *reinterpret_cast<f32x4*>(xr + c) = v[j];
     }
     ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
   }
@@ -113,27 +152,62 @@ __global__ __launch_bounds__(THREADS) void resid_rmsnorm_kernel(const float* __r
   }
 }
 
-// grid: (H, rows of this call); copies K rows and V^T columns into the cache
+// Copies one head's K rows and V^T columns into the cache: blocks 0 .. nk - 1
+// of a head take its K rows as one run of 16-byte chunks, the rest kVtRows dims
+// of V^T each, consecutive threads along the positions of a dim (a column of
+// V^T per block, 2 bytes in every cache line, took 18 us for 512 positions of
+// 32 heads of 128).
+constexpr int kVtRows = 16;
+constexpr int kCopyChunks = 4;   // 16-byte chunks of K per thread
 template <typename T>
 __global__ __launch_bounds__(kRowThreads) void kv_store_kernel(const T* __restrict__ k, const T* __restrict__ vt,
                                                                int seq, int hd, int vt_ld, T* __restrict__ ck,
-                                                               T* __restrict__ cvt, int cap, int off) {
-  const int h = blockIdx.x, s = blockIdx.y;
-  for (int c = threadIdx.x; c < hd; c += kRowThreads) {
-    ck[(size_t(h) * cap + off + s) * hd + c] = k[(size_t(h) * seq + s) * hd + c];
-    cvt[(size_t(h) * hd + c) * cap + off + s] = vt[(size_t(h) * hd + c) * vt_ld + s];
+                                                               T* __restrict__ cvt, int cap, int off, int nk,
+                                                               bool wide) {
+  const int h = blockIdx.x;
+  if (int(blockIdx.y) < nk) {
+    if (!wide) {   // a cache that starts off a 16-byte boundary
+      for (int e = blockIdx.y * kRowThreads + threadIdx.x; e < seq * hd; e += nk * kRowThreads)
+        ck[(size_t(h) * cap + off) * hd + e] = k[size_t(h) * seq * hd + e];
+      return;
+    }
+    // head_dim rows are whole chunks, and so 16-byte aligned in both where the bases are
+    const int n = seq * hd * int(sizeof(T)) / 16;
+    const u32x4* src = reinterpret_cast<const u32x4*>(k + size_t(h) * seq * hd);
+    u32x4* dst = reinterpret_cast<u32x4*>(ck + (size_t(h) * cap + off) * hd);
+    const int c0 = blockIdx.y * kCopyChunks * kRowThreads + threadIdx.x;
+    u32x4 v[kCopyChunks];
+#pragma unroll
+    for (int i = 0; i < kCopyChunks; ++i) v[i] = src[min(c0 + i * kRowThreads, n - 1)];
+#pragma unroll
+    for (int i = 0; i < kCopyChunks; ++i)
+      if (c0 + i * kRowThreads < n) dst[c0 + i * kRowThreads] = v[i];
+    return;
+  }
+  const int d0 = (blockIdx.y - nk) * kVtRows;   // head_dim is a multiple of kVtRows
+  const T* src = vt + (size_t(h) * hd + d0) * vt_ld;
+  T* dst = cvt + (size_t(h) * hd + d0) * cap + off;
+  for (int s = threadIdx.x; s < seq; s += kRowThreads) {
+    T v[kVtRows];
+#pragma unroll
+    for (int d = 0; d < kVtRows; ++d) v[d] = src[size_t(d) * vt_ld + s];
+#pragma unroll
+    for (int d = 0; d < kVtRows; ++d) dst[size_t(d) * cap + s] = v[d];
   }
 }
 
 }  // namespace
 
-hipError_t embed(int dtype, const int32_t* tok, int rows, const void* emb, int d, int vocab, float* x, hipStream_t s) {
+hipError_t embed_rmsnorm(int dtype, const int32_t* tok, int rows, const void* emb, int d, int vocab, float eps,
+                         float* x, void* out, hipStream_t s) {
+  if (d % 4 || d > kNormChunks * kRowThreads * 4) return hipErrorInvalidValue;
+  const bool wide = reinterpret_cast<uintptr_t>(emb) % 16 == 0;
   if (dtype)
-    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(rows), dim3(kRowThreads), 0, s, tok,
-                       static_cast<const bf16_t*>(emb), d, vocab, x);
+    hipLaunchKernelGGL(embed_rmsnorm_kernel<bf16_t>, dim3(rows), dim3(kRowThreads), 0, s, tok,
+                       static_cast<const bf16_t*>(emb), d, vocab, eps, x, static_cast<bf16_t*>(out), wide);
   else
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(rows), dim3(kRowThreads), 0, s, tok,
-                       static_cast<const float*>(emb), d, vocab, x);
+    hipLaunchKernelGGL(embed_rmsnorm_kernel<float>, dim3(rows), dim3(kRowThreads), 0, s, tok,
+                       static_cast<const float*>(emb), d, vocab, eps, x, static_cast<float*>(out), wide);
   return hipGetLastError();
 }
 
@@ -150,39 +224,39 @@ hipError_t rmsnorm(int dtype, const float* x, int d, float eps, int rows, const 
 }
 
 hipError_t resid_rmsnorm(int dtype, const float* part, int splits, int np, int M, float* x, int d, float eps,
-                         void* out, hipStream_t s) {
+                         int rows, const int32_t* pos, int n_pos, int seq, void* out, hipStream_t s) {
   if (d % 4 || np % 4 || d > kNormChunks * kRowThreads * 4) return hipErrorInvalidValue;
   // Fewer rows than CUs: 1024 threads per row, so that each thread walks the
   // partials of fewer columns with more loads in flight.
-  const bool wide = M < kFewRows;
-  if (dtype) {
-    if (wide)
-      hipLaunchKernelGGL((resid_rmsnorm_kernel<bf16_t, kWideThreads>), dim3(M), dim3(kWideThreads), 0, s, part,
-                         splits, np, M, x, d, eps, static_cast<bf16_t*>(out));
-    else
-      hipLaunchKernelGGL((resid_rmsnorm_kernel<bf16_t, kRowThreads>), dim3(M), dim3(kRowThreads), 0, s, part,
-                         splits, np, M, x, d, eps, static_cast<bf16_t*>(out));
-  } else {
-    if (wide)
-      hipLaunchKernelGGL((resid_rmsnorm_kernel<float, kWideThreads>), dim3(M), dim3(kWideThreads), 0, s, part,
-                         splits, np, M, x, d, eps, static_cast<float*>(out));
-    else
-      hipLaunchKernelGGL((resid_rmsnorm_kernel<float, kRowThreads>), dim3(M), dim3(kRowThreads), 0, s, part,
-                         splits, np, M, x, d, eps, static_cast<float*>(out));
-  }
+  auto go = [&](auto kern, int threads, auto* o) {
+    hipLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, part, splits, np, M, x, d, eps, pos, n_pos, seq, o);
+  };
+  const bool wide = rows < kFewRows;
+  bf16_t* ob = static_cast<bf16_t*>(out);
+  float* of = static_cast<float*>(out);
+  if (dtype)
+    wide ? go(resid_rmsnorm_kernel<bf16_t, kWideThreads>, kWideThreads, ob)
+         : go(resid_rmsnorm_kernel<bf16_t, kRowThreads>, kRowThreads, ob);
+  else
+    wide ? go(resid_rmsnorm_kernel<float, kWideThreads>, kWideThreads, of)
+         : go(resid_rmsnorm_kernel<float, kRowThreads>, kRowThreads, of);
   return hipGetLastError();
 }
 
 hipError_t kv_store(int dtype, const void* k, const void* vt, int H, int seq, int hd, int vt_ld, void* ck,
                     void* cvt, int cap, int off, hipStream_t s) {
+  const int nk = cdiv(cdiv(seq * hd * (dtype ? 2 : 4), 16), kCopyChunks * kRowThreads);
+  if (hd % kVtRows) return hipErrorInvalidValue;
+  const dim3 grid(H, nk + hd / kVtRows);
+  const bool wide = (reinterpret_cast<uintptr_t>(ck) | reinterpret_cast<uintptr_t>(k)) % 16 == 0;
   if (dtype)
-    hipLaunchKernelGGL(kv_store_kernel<bf16_t>, dim3(H, seq), dim3(kRowThreads), 0, s,
-                       static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(vt), seq, hd, vt_ld,
-                       static_cast<bf16_t*>(ck), static_cast<bf16_t*>(cvt), cap, off);
+    hipLaunchKernelGGL(kv_store_kernel<bf16_t>, grid, dim3(kRowThreads), 0, s, static_cast<const bf16_t*>(k),
+                       static_cast<const bf16_t*>(vt), seq, hd, vt_ld, static_cast<bf16_t*>(ck),
+                       static_cast<bf16_t*>(cvt), cap, off, nk, wide);
   else
-    hipLaunchKernelGGL(kv_store_kernel<float>, dim3(H, seq), dim3(kRowThreads), 0, s,
-                       static_cast<const float*>(k), static_cast<const float*>(vt), seq, hd, vt_ld,
-                       static_cast<float*>(ck), static_cast<float*>(cvt), cap, off);
+    hipLaunchKernelGGL(kv_store_kernel<float>, grid, dim3(kRowThreads), 0, s, static_cast<const float*>(k),
+                       static_cast<const float*>(vt), seq, hd, vt_ld, static_cast<float*>(ck),
+                       static_cast<float*>(cvt), cap, off, nk, wide);
   return hipGetLastError();
 }
 

@@ -134,3 +134,53 @@ def test_forward_bf16_row_tiles(P, hd, B_, S):
         print(compare_stats({k: v[b * n:(b + 1) * n] for k, v in got.items()}, ref, 2e-2, max_exceptions=2,
                             id_ranks=4, label=f"bf16 hd {hd} {B_} x {S} seq {b}"))
     model.close()
+
+
+# packed attention: 64 heads x 512 rows is the first size whose 128-query
+# workgroups fill the CUs, 64 x 384 takes 32-query ones; blocks smaller than a
+# workgroup's queries, and shared rows that end inside one
+@pytest.mark.parametrize("S,b0,B,n", [(256, 32, 64, 4), (128, 0, 64, 4), (112, 48, 16, 15)])
+def test_packed_attention_layouts(P, S, b0, B, n):
+    shape = ModelShape(n_layers=1, d_model=4096, n_heads=64, head_dim=64, d_ffn=128, vocab=500)
+    w_np = synth.model_weights_np(shape, seed=5, dtype="f32")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV) for k, v in w_np.items()}, dtype="f32", max_pos=256)
+    shared = synth.tokens_np(S, "shared", S, shape.vocab - 1)
+    shared[b0 + 3:b0 + B] = shape.mask_id
+    blocks = np.tile(shared[b0:b0 + B], (n, 1))
+    blocks[np.arange(n), 3 + np.arange(n) % (B - 3)] = np.arange(n) + 7
+    packed = np.concatenate([shared, blocks.reshape(-1)])
+    lm_pos = np.array([b0, b0 + B // 2, b0 + B - 1], dtype=np.int32)
+    out = model.forward_packed(torch.from_numpy(packed).to(DEV), S, b0, B, n, torch.from_numpy(lm_pos).to(DEV))
+    torch.cuda.synchronize()
+    logits = om.packed_logits(packed, w_np, shape, S, b0, B, n, lm_pos)
+    print(compare_stats(out.numpy(), softmax_stats(logits.reshape(-1, shape.vocab), 16), 1e-4,
+                        label=f"packed S{S} b0{b0} B{B} n{n}"))
+    model.close()
+
+
+# prefix cache writes: a cache off a 16-byte boundary, an offset into it, and
+# a length that fills no whole chunk of positions; the rest stays untouched
+@pytest.mark.parametrize("S,off,shift", [(37, 0, 0), (300, 5, 0), (64, 3, 1)])
+def test_kv_out_alignment(P, S, off, shift):
+    from paper_2608_11742_amd._abi import KvCache
+    shape = ModelShape(n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=128, vocab=300)
+    w_np = synth.model_weights_np(shape, seed=6, dtype="f32")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV) for k, v in w_np.items()}, dtype="f32", max_pos=512)
+    cap = (off + S + 15) // 8 * 8
+    n = shape.n_layers * shape.n_heads * cap * shape.head_dim
+    kb, vb = (torch.full((n + 8,), 9.0, device=DEV) for _ in range(2))
+    kv = KvCache(kb[shift:].data_ptr(), vb[shift:].data_ptr(), 0, cap)
+    toks = synth.tokens_np(9, "t", S, shape.vocab - 1)
+    model.forward(torch.from_numpy(toks).to(DEV)[None], torch.zeros(1, dtype=torch.int32, device=DEV), pos_offset=off,
+                  kv_out=kv)
+    torch.cuda.synchronize()
+    got_k = kb[shift:shift + n].cpu().numpy().reshape(2, 4, cap, 64)
+    got_v = vb[shift:shift + n].cpu().numpy().reshape(2, 4, 64, cap)
+    collect = []
+    om.hidden(toks, w_np, shape, pos_offset=off, collect=collect)
+    for l, (k, v) in enumerate(collect):
+        assert np.allclose(got_k[l, :, off:off + S], k, atol=1e-4)
+        assert np.allclose(got_v[l, :, :, off:off + S].transpose(0, 2, 1), v, atol=1e-4)
+    rest = np.setdiff1d(np.arange(cap), np.arange(off, off + S))
+    assert (got_k[:, :, rest] == 9.0).all() and (got_v[..., rest] == 9.0).all()
+    model.close()
