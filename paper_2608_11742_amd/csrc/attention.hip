@@ -495,13 +495,25 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(AttnArgs a, int kv_split
   const int q = blockIdx.x, h = blockIdx.y, b = blockIdx.z, dim = threadIdx.x;
   const size_t bh = size_t(b) * a.H + h, stride = size_t(a.B) * a.H * a.Sq * kv_rec(HD);
   const float* rec = a.kv_part + (bh * a.Sq + q) * kv_rec(HD);
+  // every range's record in flight at once (ranges past kv_splits repeat the
+  // last and are not added)
+  float ms[kKvMaxSplits], ls[kKvMaxSplits], os[kKvMaxSplits];
+#pragma unroll
+  for (int ks = 0; ks < kKvMaxSplits; ++ks) {
+    const float* r = rec + min(ks, kv_splits - 1) * stride;
+    ms[ks] = r[HD];
+    ls[ks] = r[HD + 1];
+    os[ks] = r[dim];
+  }
   float m = -INFINITY;
-  for (int ks = 0; ks < kv_splits; ++ks) m = fmaxf(m, rec[ks * stride + HD]);
+#pragma unroll
+  for (int ks = 0; ks < kKvMaxSplits; ++ks) m = fmaxf(m, ms[ks]);
   float o = 0.f, l = 0.f;
-  for (int ks = 0; ks < kv_splits; ++ks) {
-    const float w = __builtin_amdgcn_exp2f(rec[ks * stride + HD] - m);
-    o += rec[ks * stride + dim] * w;
-    l += rec[ks * stride + HD + 1] * w;
+#pragma unroll
+  for (int ks = 0; ks < kKvMaxSplits; ++ks) {
+    const float w = ks < kv_splits ? __builtin_amdgcn_exp2f(ms[ks] - m) : 0.f;
+    o += ks < kv_splits ? os[ks] * w : 0.f;
+    l += ks < kv_splits ? ls[ks] * w : 0.f;
   }
   store_f(static_cast<T*>(a.o) + (size_t(b) * a.Sq + q) * (size_t(a.H) * HD) + size_t(h) * HD + dim, o / l);
 }

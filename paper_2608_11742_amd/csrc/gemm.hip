@@ -119,9 +119,9 @@ GemmPlan plan_bf16(int kind, int M, int N, int K) {
     }
   };
   if (kind == GEMM_KIND_RESID) {
-    // parts are summed by the norm that follows, which reads each once more
+    // parts are written, and read by the norm that follows
     for (int p = 1; p <= 16 && (p == 1 || stages / p >= 4); p *= 2) {
-      const double extra = p > 1 ? parts_us(M, N, p) : 0.0;
+      const double extra = p > 1 ? 2.0 * parts_us(M, N, p) : 0.0;
       offer(T_BIG, p, extra);
       if (p > 1) offer(T_QUAD, p, extra);
       offer(T_128x128, p, extra);

@@ -381,19 +381,20 @@ __device__ __forceinline__ void wave_sort(float& v, int& i) {
 }
 
 // One workgroup of W = blockDim.x / 64 waves per row (W grows with the number
-// of partials).  The row's top 16 lie in few of its partials' sorted lists: a
-// wave sorts its lanes' best list heads, and the 16th of them is a bound that
-// at least 16 logits of the row reach, so only the entries no worse than the
-// best wave's bound are candidates (a few hundred of P * 16).  They are
+// of partials).  The row's top 16 lie in few of its partials' sorted lists:
+// the waves sort their lanes' best list heads, and then the best 16 of every
+// wave; the 16th is a bound that at least 16 logits of the row reach, so only
+// the entries no worse than it are candidates (some 30 of P * 16).  They are
 // gathered in LDS and wave 0 sorts them, 48 at a time behind the best 16 so far.
-// Latency bound.  32 rows of 1024 partials 44 -> 13 us, of 2048 64 -> 23
-// against folding every list into a per-lane top 16.  Ranking heads and
-// candidates by counting instead of sorting took 28 us for 2048; merging the
-// lists of a row's scan threads in pass 1 took as long there as it saved here.
+// Latency bound.  Folding every list into a per-lane top 16 took 44 us for 32
+// rows of 1024 partials and 64 us for 2048; a bound per wave instead of per row
+// 23 us for 2048 (some 300 candidates, sorted one 48 after the other); ranking
+// by counting instead of sorting 28 us; contiguous copies of the list heads and
+// merging the lists of a row's scan threads in pass 1 gained nothing.
 __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsOut out) {
   constexpr int kMaxW = 8, kCap = 1024;
-  __shared__ float red_m[kMaxW], red_s[kMaxW], red_t[kMaxW], bound_v[kMaxW];
-  __shared__ int bound_i[kMaxW];
+  __shared__ float red_m[kMaxW], red_s[kMaxW], red_t[kMaxW], top_v[kMaxW * kK];
+  __shared__ int top_i[kMaxW * kK];
   __shared__ float cv[kCap];
   __shared__ int ci[kCap];
   __shared__ int n_cand;
@@ -412,17 +413,21 @@ __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsO
   }
   M = wave_max(M);
   wave_sort(hv, hi);
-  if (lane == kK - 1) { bound_v[wave] = hv; bound_i[wave] = hi; }
+  if (lane < kK) { top_v[wave * kK + lane] = hv; top_i[wave * kK + lane] = hi; }
   if (lane == 0) red_m[wave] = M;
   if (threadIdx.x == 0) n_cand = 0;
   __syncthreads();
   M = red_m[0];
-  float bv = bound_v[0];
-  int bi = bound_i[0];
-  for (int w = 1; w < W; ++w) {
-    M = fmaxf(M, red_m[w]);
-    if (better(bound_v[w], bound_i[w], bv, bi)) { bv = bound_v[w]; bi = bound_i[w]; }
+  for (int w = 1; w < W; ++w) M = fmaxf(M, red_m[w]);
+  if (W > 1) {   // every wave: the better of the waves' heads l and l + 64 in lane l, sorted
+    const int e2 = lane + 64;
+    hv = lane < W * kK ? top_v[lane] : -INFINITY;
+    hi = lane < W * kK ? top_i[lane] : 0x7fffffff;
+    if (e2 < W * kK && better(top_v[e2], top_i[e2], hv, hi)) { hv = top_v[e2]; hi = top_i[e2]; }
+    wave_sort(hv, hi);
   }
+  const float bv = __shfl(hv, kK - 1, 64);
+  const int bi = __shfl(hi, kK - 1, 64);
   float S = 0.f, Tt = 0.f;
   for (int p = threadIdx.x; p < part.P; p += blockDim.x) {
     const float mp = part.m[base + p];
