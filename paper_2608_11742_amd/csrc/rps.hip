@@ -25,7 +25,7 @@ struct StatsIn {
   int k;
 };
 
-// block-wide (value, id) argmax over 256 threads; result valid in every thread
+// block-wide (value, id) argmax over up to 1024 threads; result valid in every thread
 __device__ void block_argmax(float& v, int& i, float* sv, int* si) {
   wave_argmax(v, i);
   const int w = threadIdx.x >> 6;
@@ -33,108 +33,121 @@ __device__ void block_argmax(float& v, int& i, float* sv, int* si) {
   __syncthreads();
   v = sv[0];
   i = si[0];
-  for (int k = 1; k < kT / kWave; ++k)
+  for (int k = 1; k < int(blockDim.x) / kWave; ++k)
     if (better(sv[k], si[k], v, i)) { v = sv[k]; i = si[k]; }
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kT) void select_kernel(StatsIn st, const int32_t* __restrict__ m_pos, int n_m,
-                                                    rps_params prm, rps_plan* __restrict__ plan) {
+// One thread per masked row (256, 512 or 1024 threads).
+__global__ __launch_bounds__(kMaxM) void select_kernel(StatsIn st, const int32_t* __restrict__ m_pos, int n_m,
+                                                       rps_params prm, rps_plan* __restrict__ plan) {
   __shared__ float sh_sort[kMaxM];
-  __shared__ float sh_htr[kMaxM];
-  __shared__ uint8_t sh_feas[kMaxM];
-  __shared__ float red_v[4];
-  __shared__ int red_i[4];
+  __shared__ float red_v[kMaxM / kWave];
+  __shared__ int red_i[kMaxM / kWave];
   __shared__ int chosen[RPS_MAX_PIVOTS];
-  __shared__ float band[2];
-  __shared__ float piv_logit[RPS_MAX_PIVOTS][DLLM_MAX_TOPK], piv_lse[RPS_MAX_PIVOTS];
-  __shared__ int piv_id[RPS_MAX_PIVOTS][DLLM_MAX_TOPK], piv_pos[RPS_MAX_PIVOTS];
-  __shared__ uint8_t reach[RPS_MAX_PIVOTS][DLLM_MAX_TOPK];
+  __shared__ int piv_cnt[RPS_MAX_PIVOTS], piv_slot[RPS_MAX_PIVOTS], piv_first[RPS_MAX_PIVOTS];
   __shared__ rps_plan pl;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, j = tid;   // this thread's row
+  const bool own = j < n_m;
   const int kmax = min(prm.k_max, st.k);
 
-  // truncated support T_i = top-k_max: mass mu_i and -sum p log p (Eq. 3), not renormalised
-  for (int j = tid; j < n_m; j += kT) {
+  // truncated support T_i = top-k_max: mass mu_i and -sum p log p (Eq. 3), not
+  // renormalised; every load in flight before the first sum
+  float htr = -INFINITY, ent = INFINITY;
+  int pos = 0x7fffffff;
+  bool feas = false;
+  if (own) {
+    float lg[DLLM_MAX_TOPK];
     const float lse = st.lse[j];
+    ent = st.H[j];
+    pos = m_pos[j];
+#pragma unroll
+    for (int k = 0; k < DLLM_MAX_TOPK; ++k)
+      lg[k] = st.topk_logit[size_t(j) * st.k + min(k, kmax - 1)];
     float mu = 0.f, ht = 0.f;
-    for (int k = 0; k < kmax; ++k) {
-      const float lp = st.topk_logit[size_t(j) * st.k + k] - lse;
-      const float p = expf(lp);
-      mu += p;
-      ht -= p * lp;
-    }
-    sh_htr[j] = ht;
-    sh_feas[j] = prm.mode == RPS_PIVOT_PAPER ? (mu >= prm.tau_pivot) : 0;
-    sh_sort[j] = st.H[j];
+#pragma unroll
+    for (int k = 0; k < DLLM_MAX_TOPK; ++k)
+      if (k < kmax) {
+        const float lp = lg[k] - lse;
+        const float p = expf(lp);
+        mu += p;
+        ht -= p * lp;
+      }
+    htr = ht;
+    feas = prm.mode == RPS_PIVOT_PAPER && mu >= prm.tau_pivot;
   }
   if (prm.mode == RPS_PIVOT_BAND) {
-    // bitonic sort of H over M (padded with +inf) for the percentile band
+    // bitonic sort of H over M (padded with +inf) for the percentile band, one
+    // value per thread: partners within a wave by shuffles, others through LDS
     int n2 = 1;
     while (n2 < n_m) n2 <<= 1;
-    for (int j = n_m + tid; j < n2; j += kT) sh_sort[j] = INFINITY;
-    __syncthreads();
+    float v = ent;
     for (int size = 2; size <= n2; size <<= 1)
       for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        for (int x = tid; x < n2 / 2; x += kT) {
-          const int lo = 2 * x - (x & (stride - 1));
-          const int hi = lo + stride;
-          const bool up = (lo & size) == 0;
-          const float a = sh_sort[lo], b = sh_sort[hi];
-          if ((a > b) == up) { sh_sort[lo] = b; sh_sort[hi] = a; }
+        float w;
+        if (stride < kWave) {
+          w = __shfl_xor(v, stride, kWave);
+        } else {
+          __syncthreads();
+          sh_sort[tid] = v;
+          __syncthreads();
+          w = sh_sort[tid ^ stride];
         }
-        __syncthreads();
+        // ascending blocks keep the smaller value in the lower thread
+        const bool up = (tid & size) == 0, lower = (tid & stride) == 0;
+        const float a = lower ? v : w, b = lower ? w : v;   // values of the lower and the upper thread
+        if ((a > b) == up) v = w;
       }
-    if (tid == 0) {
-      for (int e = 0; e < 2; ++e) {
-        const float q = (e ? prm.pct_hi : prm.pct_lo) / 100.0f;
-        const float idx = q * float(n_m - 1);
-        const int lo = min(int(floorf(idx)), n_m - 1);
-        const int hi = min(lo + 1, n_m - 1);
-        band[e] = sh_sort[lo] + (idx - float(lo)) * (sh_sort[hi] - sh_sort[lo]);
-      }
-    }
     __syncthreads();
-    for (int j = tid; j < n_m; j += kT) {
-      const float h = st.H[j];
-      sh_feas[j] = h >= band[0] && h <= band[1];
+    sh_sort[tid] = v;
+    __syncthreads();
+    float band[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float q = (e ? prm.pct_hi : prm.pct_lo) / 100.0f;
+      const float idx = q * float(n_m - 1);
+      const int lo = min(int(floorf(idx)), n_m - 1);
+      const int hi = min(lo + 1, n_m - 1);
+      band[e] = sh_sort[lo] + (idx - float(lo)) * (sh_sort[hi] - sh_sort[lo]);
     }
+    feas = own && ent >= band[0] && ent <= band[1];
   }
-  __syncthreads();
 
   // the n_pivots feasible rows of largest truncated entropy (lower position first on ties)
   const int n_piv = n_m > 1 ? min(prm.n_pivots, RPS_MAX_PIVOTS) : 0;
   if (tid < RPS_MAX_PIVOTS) chosen[tid] = -1;
-  __syncthreads();
   for (int rnd = 0; rnd < n_piv; ++rnd) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int j = tid; j < n_m; j += kT)
-      if (sh_feas[j] && better(sh_htr[j], m_pos[j], bv, bi)) { bv = sh_htr[j]; bi = m_pos[j]; }
+    const bool in = feas && htr == htr;   // a NaN is never chosen
+    float bv = in ? htr : -INFINITY;
+    int bi = in ? pos : 0x7fffffff;
     block_argmax(bv, bi, red_v, red_i);
-    for (int j = tid; j < n_m; j += kT)
-      if (sh_feas[j] && m_pos[j] == bi && bi != 0x7fffffff) { chosen[rnd] = j; sh_feas[j] = 0; }
-    __syncthreads();
+    if (in && pos == bi) {
+      chosen[rnd] = j;
+      feas = false;
+    }
   }
+  __syncthreads();
 
   // adaptive candidate sets: v in T_{i*} with p(v) >= r P^max, rank order,
-  // capped.  One thread per (pivot, rank) loads and tests, thread 0 counts in
-  // LDS and all write the plan: a chain of global loads in one thread took
-  // half of this kernel's time.
-  static_assert(RPS_MAX_PIVOTS * DLLM_MAX_TOPK == kT, "one thread per pivot and rank");
-  {
-    const int rnd = tid / DLLM_MAX_TOPK, k = tid % DLLM_MAX_TOPK;
-    const int j = rnd < n_piv ? chosen[rnd] : -1;
-    if (j >= 0 && k < kmax) {
-      const float lg = st.topk_logit[size_t(j) * st.k + k];
-      piv_logit[rnd][k] = lg;
-      piv_id[rnd][k] = st.topk_id[size_t(j) * st.k + k];
-      reach[rnd][k] = expf(lg - st.lmax[j]) >= prm.r;   // p(v) / P^max is non-increasing in rank
-      if (k == 0) {
-        piv_lse[rnd] = st.lse[j];
-        piv_pos[rnd] = m_pos[j];
-      }
+  // capped.  One thread per (pivot, rank) loads, tests and writes its branch;
+  // thread 0 only adds up the pivots' counts.  A single thread walking the
+  // ranks took half of this kernel's time.
+  static_assert(RPS_MAX_PIVOTS * DLLM_MAX_TOPK == kT && kWave % DLLM_MAX_TOPK == 0, "one thread per pivot and rank");
+  const int rnd = tid / DLLM_MAX_TOPK, k = tid % DLLM_MAX_TOPK;
+  const int pj = rnd < n_piv ? chosen[rnd] : -1;   // pivots after the first missing one are missing too
+  float lg = 0.f, lse_p = 0.f;
+  int id = 0, pos_p = 0;
+  if (tid < kT) {
+    bool reach = false;
+    if (pj >= 0 && k < kmax) {
+      lg = st.topk_logit[size_t(pj) * st.k + k];
+      id = st.topk_id[size_t(pj) * st.k + k];
+      lse_p = st.lse[pj];
+      pos_p = m_pos[pj];
+      reach = expf(lg - st.lmax[pj]) >= prm.r;   // p(v) / P^max is non-increasing in rank
     }
+    const unsigned r16 = unsigned(__ballot(reach) >> ((tid & 63) / DLLM_MAX_TOPK * DLLM_MAX_TOPK)) & 0xffffu;
+    if (k == 0) piv_cnt[rnd] = __builtin_ctz(~r16);   // ranks before the first that fails
   }
   if (tid < RPS_MAX_PIVOTS) pl.pivot_row[tid] = pl.pivot_pos[tid] = pl.n_cand[tid] = -1;
   if (tid < RPS_MAX_BRANCH) {
@@ -145,30 +158,35 @@ __global__ __launch_bounds__(kT) void select_kernel(StatsIn st, const int32_t* _
   if (tid == 0) {
     int np = 0, nb = 0;
     const int cap = min(prm.max_branch, RPS_MAX_BRANCH);
-    for (int rnd = 0; rnd < n_piv; ++rnd) {
-      const int j = chosen[rnd];
-      if (j < 0) break;
-      int cnt = 0;
-      for (int k = 0; k < kmax && cnt < prm.n_cand && nb + cnt < cap && reach[rnd][k]; ++k) ++cnt;
-      if (cnt < 2) continue;
-      pl.pivot_row[np] = j;
-      pl.pivot_pos[np] = piv_pos[rnd];
-      pl.n_cand[np] = cnt;
-      for (int k = 0; k < cnt; ++k, ++nb) {
-        pl.br_pivot[nb] = np;
-        pl.br_row[nb] = j;
-        pl.br_pos[nb] = piv_pos[rnd];
-        pl.br_token[nb] = piv_id[rnd][k];
-        pl.br_logp[nb] = piv_logit[rnd][k] - piv_lse[rnd];
-      }
-      ++np;
+    for (int q = 0; q < n_piv; ++q) {
+      const int cnt = min(min(piv_cnt[q], prm.n_cand), cap - nb);
+      const bool take = cnt >= 2;
+      piv_cnt[q] = take ? cnt : 0;
+      piv_slot[q] = np;
+      piv_first[q] = nb;
+      np += take;
+      nb += take ? cnt : 0;
     }
     pl.n_pivots = np;
     pl.n_branch = nb;
   }
   __syncthreads();
+  if (tid < kT && rnd < n_piv && k < piv_cnt[rnd]) {
+    const int p = piv_slot[rnd], b = piv_first[rnd] + k;
+    if (k == 0) {
+      pl.pivot_row[p] = pj;
+      pl.pivot_pos[p] = pos_p;
+      pl.n_cand[p] = piv_cnt[rnd];
+    }
+    pl.br_pivot[b] = p;
+    pl.br_row[b] = pj;
+    pl.br_pos[b] = pos_p;
+    pl.br_token[b] = id;
+    pl.br_logp[b] = lg - lse_p;
+  }
+  __syncthreads();
   static_assert(sizeof(rps_plan) % 4 == 0, "plan words");
-  for (int w = tid; w < int(sizeof(rps_plan) / 4); w += kT)
+  for (int w = tid; w < int(sizeof(rps_plan) / 4); w += blockDim.x)
     reinterpret_cast<int*>(plan)[w] = reinterpret_cast<const int*>(&pl)[w];
 }
 
@@ -453,7 +471,8 @@ StatsIn to_in(const StatsOut& s) { return StatsIn{s.H, s.lse, s.lmax, s.argmax, 
 
 hipError_t rps_select(const StatsOut& base, const int32_t* m_pos, int n_m, const rps_params& prm, rps_plan* plan,
                       hipStream_t s) {
-  hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kT), 0, s, to_in(base), m_pos, n_m, prm, plan);
+  const int threads = n_m <= kT ? kT : n_m <= 2 * kT ? 2 * kT : kMaxM;
+  hipLaunchKernelGGL(select_kernel, dim3(1), dim3(threads), 0, s, to_in(base), m_pos, n_m, prm, plan);
   return hipGetLastError();
 }
 
