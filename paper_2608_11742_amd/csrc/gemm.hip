@@ -137,8 +137,9 @@ GemmPlan plan_bf16(int kind, int M, int N, int K) {
   // one pass with the epilogue fused
   for (Tile t : {T_BIG, T_MID, T_128x192, T_128x128}) offer(t, 1, 0.0);
   if (kind == GEMM_KIND_QKV && M <= 512 && N % Mid::BN == 0)
-    // 256 x 192 parts and a launch that sums them
-    for (int p = 2; p <= 16 && stages / p >= 4; p *= 2) offer(T_MID, p, 2.0 + parts_us(M, N, p));
+    // 256 x 192 parts and a launch that sums them, 5 us and a read of each part
+    // (d 4096: 512 rows in one pass gain 2.5 us a layer, 320 and 400 rows lose 1)
+    for (int p = 2; p <= 16 && stages / p >= 4; p *= 2) offer(T_MID, p, 5.0 + parts_us(M, N, p));
   return best;
 }
 

@@ -87,11 +87,15 @@ int lm_tile(int dtype, int R, int V) {
   if (R <= 64 || few) return 64;
   if (R <= 128) return 128;
   if (R > 32768) return 256;   // 2 partials a row and slice instead of 4
-  if (!dtype) return 128;      // the fp32 matrix cores bound every tile
+  const int t128 = tile_times(128, R, V, slices_for(128, R, V));
+  // the fp32 matrix cores bound every tile: two 64 x 128 ones share a CU, so
+  // each takes half the time of a 128 x 256 one (352 rows, vocabulary 32000: 3
+  // against 2 tile times, 252 against 317 us; 512 rows: 4 against 2, 320 both)
+  if (!dtype) return tile_times(64, R, V, slices_for(64, R, V)) < 2 * t128 ? 64 : 128;
   // d 4096: a 128 x 256 tile takes about 73 us, a 256 x 256 tile 1.72 times
   // that (352 rows, vocabulary 126464: 6 against 4 tile times, 472 against
   // 537 us; 512 rows: 8 against 4, 602 against 554)
-  const int t128 = tile_times(128, R, V, slices_for(128, R, V)), t256 = tile_times(256, R, V, slices_for(256, R, V));
+  const int t256 = tile_times(256, R, V, slices_for(256, R, V));
   return 100 * t128 < 172 * t256 ? 128 : 256;
 }
 
