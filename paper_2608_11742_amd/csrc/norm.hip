@@ -18,7 +18,9 @@ __device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
 __device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
 
 constexpr int kNormChunks = 8;   // 16-byte chunks per thread held in registers: d <= 8192
-constexpr int kFewRows = 256;    // fewer rows than CUs: resid_rmsnorm takes kWideThreads per row
+// resid_rmsnorm: 1024 threads a row, so that each walks the partials of one or
+// two chunks with every load in flight (512 rows of 8 parts, d 4096: a 265 us
+// layer gains 1.3 us over 256 threads a row, 1536 rows 4)
 constexpr int kWideThreads = 1024;
 
 // One workgroup per output row; the row stays in registers between the sum
@@ -104,13 +106,14 @@ __global__ __launch_bounds__(kRowThreads) void embed_rmsnorm_kernel(const int32_
 // out[r] = x[r] / sqrt(mean(x[r]^2) + eps).  With pos (the final norm): output
 // row r reads row src(r) as in rmsnorm_kernel, and x, which nothing reads
 // after it, is not written back.
-template <typename T, int THREADS>
-__global__ __launch_bounds__(THREADS) void resid_rmsnorm_kernel(const float* __restrict__ part, int splits, int np,
+template <typename T>
+__global__ __launch_bounds__(kWideThreads) void resid_rmsnorm_kernel(const float* __restrict__ part, int splits, int np,
                                                                 int M, float* __restrict__ x, int d, float eps,
                                                                 const int32_t* __restrict__ pos, int n_pos, int seq,
                                                                 T* __restrict__ out) {
+  constexpr int THREADS = kWideThreads;
   constexpr int CH = kNormChunks * kRowThreads / THREADS;   // 16-byte chunks per thread: d <= 8192
-  constexpr int LIF = CH <= 2 ? 8 : 4;                       // partial loads in flight per chunk
+  constexpr int LIF = 8;                                     // partial loads in flight per chunk
   __shared__ float red[THREADS / kWave];
   const int r = blockIdx.x;
   const int sr = pos ? (r / n_pos) * seq + min(max(pos[r % n_pos], 0), seq - 1) : r;
@@ -226,20 +229,12 @@ hipError_t rmsnorm(int dtype, const float* x, int d, float eps, int rows, const 
 hipError_t resid_rmsnorm(int dtype, const float* part, int splits, int np, int M, float* x, int d, float eps,
                          int rows, const int32_t* pos, int n_pos, int seq, void* out, hipStream_t s) {
   if (d % 4 || np % 4 || d > kNormChunks * kRowThreads * 4) return hipErrorInvalidValue;
-  // Fewer rows than CUs: 1024 threads per row, so that each thread walks the
-  // partials of fewer columns with more loads in flight.
-  auto go = [&](auto kern, int threads, auto* o) {
-    hipLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, part, splits, np, M, x, d, eps, pos, n_pos, seq, o);
-  };
-  const bool wide = rows < kFewRows;
-  bf16_t* ob = static_cast<bf16_t*>(out);
-  float* of = static_cast<float*>(out);
   if (dtype)
-    wide ? go(resid_rmsnorm_kernel<bf16_t, kWideThreads>, kWideThreads, ob)
-         : go(resid_rmsnorm_kernel<bf16_t, kRowThreads>, kRowThreads, ob);
+    hipLaunchKernelGGL(resid_rmsnorm_kernel<bf16_t>, dim3(rows), dim3(kWideThreads), 0, s, part, splits, np, M, x, d,
+                       eps, pos, n_pos, seq, static_cast<bf16_t*>(out));
   else
-    wide ? go(resid_rmsnorm_kernel<float, kWideThreads>, kWideThreads, of)
-         : go(resid_rmsnorm_kernel<float, kRowThreads>, kRowThreads, of);
+    hipLaunchKernelGGL(resid_rmsnorm_kernel<float>, dim3(rows), dim3(kWideThreads), 0, s, part, splits, np, M, x, d,
+                       eps, pos, n_pos, seq, static_cast<float*>(out));
   return hipGetLastError();
 }
 
