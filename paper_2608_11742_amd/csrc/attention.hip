@@ -138,7 +138,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a, float qk_
   // other only; a branch block's rows attend to the shared rows outside the
   // block they stand in for (b0 .. b0+pack_B-1) and to their own block.
   // Phase 1 tiles cover keys 0 .. S-1, phase 2 tiles the branch blocks that
-  // hold this workgroup's branch queries, each block on tiles of its own.
+  // hold this workgroup's branch queries, each block on tiles of its own that
+  // start at the V^T chunk of its first key: a V^T copy moves whole aligned
+  // chunks, and one started at a first key inside a chunk would run past the
+  // row's end, or be clamped there and bring other keys' values.
   constexpr bool packed = kPacked;   // a.pack_B > 0
   const int S = packed ? a.pack_S : a.Sq;
   const int n_ot = cdiv(S, kKT);
@@ -148,7 +151,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a, float qk_
     const int qlo = max(qblk * kWgQ, S), qhi = min(qblk * kWgQ + kWgQ, a.Sq);
     if (qlo < qhi) {
       jb0 = (qlo - S) / a.pack_B;
-      tpb = cdiv(a.pack_B, kKT);
+      // keys before the first of a block: S % E where blocks are whole chunks,
+      // else up to E - 1 (one tile all the same: pack_B < E)
+      tpb = cdiv(a.pack_B + (a.pack_B % C::E ? C::E - 1 : S % C::E), kKT);
       n_bt = ((qhi - 1 - S) / a.pack_B - jb0 + 1) * tpb;
     }
   }
@@ -200,14 +205,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a, float qk_
   auto src = [&](int t) -> Src {
     if (t < n_pt) return Src{Kp, Vp, t * kKT, a.p_len, a.p_cap, -1, true};
     if (t < n_pt + n_ot) return Src{Ko, Vo, (t - n_pt) * kKT, S, a.vt_ld, -1, false};
-    const int u = t - n_pt - n_ot, j = jb0 + u / tpb;
-    return Src{Ko, Vo, S + j * a.pack_B + (u % tpb) * kKT, S + (j + 1) * a.pack_B, a.vt_ld, j, false};
+    const int u = t - n_pt - n_ot, j = jb0 + u / tpb, first = S + j * a.pack_B;
+    return Src{Ko, Vo, first / C::E * C::E + (u % tpb) * kKT, first + a.pack_B, a.vt_ld, j, false};
   };
   // Copy tile t into ring slot `slot`.  Lane l of a load instruction fills
   // row l / C, slot l % C of its block and fetches the chunk the swizzle
   // assigns there.  Rows past the last valid key read the last valid row and
   // V^T chunks past the row pitch read the row's last chunk: every address
   // stays inside the source, and those keys are masked (K) or zeroed (V^T).
+  // k0 is a whole number of chunks and the pitch too, so a chunk that holds a
+  // valid key is never the one that is moved.
   auto issue = [&](int t, int slot) {
     const Src s = src(t);
     const rsrc_t rk = buffer_rsrc(s.k), rv = buffer_rsrc(s.v);
@@ -323,7 +330,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a, float qk_
             const int key = k0 + key_of(half, kk, 4 * g + i);
             bool ok = key < nk;
             if (pmask)
-              ok = ok && (sr.branch >= 0 ? qbr[qb] == sr.branch
+              ok = ok && (sr.branch >= 0 ? qbr[qb] == sr.branch && key >= nk - a.pack_B
                                          : (qbr[qb] < 0 || key < a.pack_b0 || key >= a.pack_b0 + a.pack_B));
             const float v = ok ? sc[kk][qb][i] : -INFINITY;
             p[kk][qb][i] = v;

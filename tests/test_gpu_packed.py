@@ -82,6 +82,46 @@ def test_packed_forward_tiny_f32(P, tiny, S, b0, B, n):
     print(compare_stats(out.numpy(), ref, 1e-4, label=f"packed f32 S{S} b0{b0} B{B} n{n}"))
 
 
+# Blocks that start inside a 16-byte chunk of V^T (4 fp32 or 8 binary16 keys):
+# shorter than a chunk, where the last block ends at the row's pitch, and whole
+# chunks behind an odd shared length, whose tiles hold one more key block
+@pytest.mark.parametrize("S,b0,B,n", [(100, 52, 2, 2), (103, 40, 1, 9), (100, 96, 4, 3), (101, 3, 64, 2)])
+def test_packed_forward_unaligned_blocks_tiny_f32(P, tiny, S, b0, B, n):
+    test_packed_forward_tiny_f32(P, tiny, S, b0, B, n)
+
+
+@pytest.mark.parametrize("S,b0,B,n", [(100, 52, 4, 3), (101, 50, 2, 5), (97, 64, 1, 15), (77, 8, 8, 9),
+                                      (131, 96, 32, 2), (133, 64, 64, 3)])
+def test_packed_forward_unaligned_blocks_bf16_against_mirror(P, small_bf16, S, b0, B, n):
+    shape, w_np, model = small_bf16
+    shared, packed = _packed_case(shape, S, b0, B, n, seed=60 + n)
+    lm_pos = np.arange(b0, b0 + B, dtype=np.int32)
+    out = model.forward_packed(torch.from_numpy(packed).to(DEV), S, b0, B, n, torch.from_numpy(lm_pos).to(DEV),
+                               scale=3.0)
+    torch.cuda.synchronize()
+    ref, *ref2 = [softmax_stats(om.packed_logits(packed, w, shape, S, b0, B, n, lm_pos, scale=3.0,
+                                                mirror=True).reshape(-1, shape.vocab), 16)
+                 for w in (w_np, *perturbations(w_np))]
+    print(compare_stats(out.numpy(), ref, 2e-2, max_exceptions=allowed_flips(ref, ref2), id_ranks=4,
+                        label=f"packed bf16 S{S} B{B} n{n}"), "oracle's own flips", flip_rows(ref, ref2))
+
+
+# the same in 128-query workgroups (64 heads x 4 of them fill the CUs)
+@pytest.mark.parametrize("S,b0,B,n", [(418, 32, 2, 15), (383, 200, 64, 2)])
+def test_packed_forward_unaligned_blocks_full_layout(P, S, b0, B, n):
+    shape = ModelShape(n_layers=1, d_model=4096, n_heads=64, head_dim=64, d_ffn=128, vocab=500)
+    w_np = synth.model_weights_np(shape, seed=5, dtype="f32")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV) for k, v in w_np.items()}, dtype="f32", max_pos=512)
+    _, packed = _packed_case(shape, S, b0, B, n, seed=80)
+    lm_pos = np.arange(b0, b0 + B, dtype=np.int32)
+    out = model.forward_packed(torch.from_numpy(packed).to(DEV), S, b0, B, n, torch.from_numpy(lm_pos).to(DEV))
+    torch.cuda.synchronize()
+    logits = om.packed_logits(packed, w_np, shape, S, b0, B, n, lm_pos)
+    print(compare_stats(out.numpy(), softmax_stats(logits.reshape(-1, shape.vocab), 16), 1e-4,
+                        label=f"packed S{S} b0{b0} B{B} n{n}"))
+    model.close()
+
+
 def test_packed_forward_probe(P, tiny):
     from paper_2608_11742_amd._abi import Probe
     shape, w_np, model = tiny
