@@ -78,8 +78,11 @@ __device__ __forceinline__ uint32_t pack_vt2(float a, float b) { return pack_f16
 __device__ __forceinline__ void store_vt(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_vt(bf16_t* p, float v) { p->bits = uint16_t(pack_vt2(v, 0.f)); }
 
-// silu(g) = g / (1 + e^-g) with the hardware base-2 exponential and
-// reciprocal (about 1 ulp each)
+// silu(g) = g / (1 + e^-g) with the hardware base-2 exponential
+__device__ __forceinline__ float silu(float g) {
+  return g / (1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+}
+// the same with the hardware reciprocal (about 1 ulp) in place of the division
 __device__ __forceinline__ float silu_fast(float g) {
   return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
 }

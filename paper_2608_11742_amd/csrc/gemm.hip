@@ -690,7 +690,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_direct_ke
         const int j = p0 + 16 * n;
         f32x4 v;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = silu_fast(acc[m][n][i]) * acc[m][n + kHN][i];
+        for (int i = 0; i < 4; ++i) v[i] = silu(acc[m][n][i]) * acc[m][n + kHN][i];
         T* dst = out + size_t(row) * ep.F + j;
         if (vec && j + 3 < ep.F) {
           store4(dst, v);
@@ -836,7 +836,7 @@ __global__ __launch_bounds__(kRedThreads) void splitk_swiglu_kernel(const float*
     u += *reinterpret_cast<const f32x4*>(src + p * stride + 64);
   }
 #pragma unroll
-  for (int e = 0; e < 4; ++e) store_f(out + size_t(row) * F + j + e, g[e] / (1.0f + __expf(-g[e])) * u[e]);
+  for (int e = 0; e < 4; ++e) store_f(out + size_t(row) * F + j + e, silu(g[e]) * u[e]);
 }
 
 

@@ -184,3 +184,40 @@ def test_kv_out_alignment(P, S, off, shift):
     rest = np.setdiff1d(np.arange(cap), np.arange(off, off + S))
     assert (got_k[:, :, rest] == 9.0).all() and (got_v[..., rest] == 9.0).all()
     model.close()
+
+
+# fp32 rounding of the projections, far below the tolerance of a whole forward:
+# the kernels and the inputs are fixed, so each figure is too, and each bound
+# lies half way between the two it tells apart
+def test_f32_swiglu_rounding(P):
+    """Gate values reach the output through nothing but the SwiGLU, one
+    rounding of the final norm and a factor common to the row: a token's
+    embedding is 16 in one place of 256 (its norm exact), attention is switched
+    off, the gates of a row are 16 weights of its place, every up is 1 and the
+    LM head reads the 16 sums as they are.  The error is 0.765 of 2^-24 (root
+    mean square) with a correctly rounded division behind the hardware's
+    exponential, 0.839 with the hardware's reciprocal."""
+    d, F, V, n = 256, 128, 300, 16
+    shape = ModelShape(n_layers=1, d_model=d, n_heads=4, head_dim=64, d_ffn=F, vocab=V, rms_eps=1e-30)
+    rng = np.random.default_rng(1)
+    w = {"emb": np.zeros((V, d)), "lm_head": np.zeros((V, d)), "layers.0.wqkv": np.zeros((3 * d, d)),
+         "layers.0.wo": np.zeros((d, d)), "layers.0.wgu": np.zeros((2 * F, d)), "layers.0.wdown": np.zeros((d, F))}
+    rows = np.arange(n, d)                                  # token t: 16 in place t
+    w["emb"][rows, rows] = 16.0
+    gate = rng.uniform(0.05, 4.0, (n, d)).astype(np.float32)   # 16 x weight: exact
+    w["layers.0.wgu"][:n] = gate / 16
+    w["layers.0.wgu"][F:F + n] = 1.0 / 16
+    w["layers.0.wdown"][np.arange(n), np.arange(n)] = 1.0
+    w["lm_head"][np.arange(n), np.arange(n)] = 1.0
+    model = P.Model(shape, {k: torch.from_numpy(v.astype(np.float32)).to(DEV) for k, v in w.items()}, dtype="f32",
+                    max_pos=256)
+    out = model.forward(torch.from_numpy(rows.astype(np.int32)).to(DEV)[None],
+                        torch.arange(len(rows), dtype=torch.int32, device=DEV))
+    got = out.numpy()["topk_logit"].astype(np.float64)
+    g = gate[:, rows].T.astype(np.float64)
+    ratio = got / np.sort(g / (1.0 + np.exp(-g)), 1)[:, ::-1]
+    err = ratio / ratio.mean(1, keepdims=True) - 1.0        # without the row's own factor
+    rms = np.sqrt((err ** 2).mean()) * 2.0 ** 24
+    print(f"SwiGLU rounding {rms:.3f}")
+    assert rms < 0.80
+    model.close()
