@@ -568,10 +568,12 @@ struct DirectCfg {
 // 256 x 256 tiles of 8 waves: 603 x 8192 x 1024 124 -> 89 us (114 TFLOP/s),
 // 512 x 2048 x 256 37 -> 9 us, and a d 4096 layer of 2048 rows 7.7 -> 7.1 ms;
 // 128 x 128 tiles were within 3% at 2048 rows and up to 7% slower below.  The
-// sums are folded every 256 of K: without split-K parts the error against 64
-// bits was 5.9e-7 (603 rows, K up to 4096) and 8.9e-7 where it had been 5.4e-7
-// and 5.2e-7; folding gives 5.4e-7 again for 2% of the time.
-using F32Cfg = DirectCfg<float, 64, 64, 4, 1, 4, false, 8>;
+// sums are folded every 128 of K, the shortest split-K part: error of the top
+// logits against 64 bits, mean over 8 to 24 models, in parts / folded every 256
+// / every 128: d 256, 8 x 64 rows 2.87e-7 / 3.08e-7 / 2.87e-7, d 1024, 3 x 201
+// rows 5.52e-7 / 5.51e-7 / 5.20e-7, d 2048, 2 x 512 rows 8.91e-7 / 7.33e-7 /
+// 7.13e-7.  Folding takes 2% of the time, twice as often 0.3% more.
+using F32Cfg = DirectCfg<float, 64, 64, 4, 1, 4, false, 4>;
 // bf16 tiles, 8 (64 x 128: 4) waves, early-release schedule; plan_bf16 says
 // where each is used
 using D256x192 = DirectCfg<bf16_t, 256, 192, 4, 2, 2, true>;

@@ -221,3 +221,26 @@ def test_f32_swiglu_rounding(P):
     print(f"SwiGLU rounding {rms:.3f}")
     assert rms < 0.80
     model.close()
+
+
+@pytest.mark.parametrize("B_,S", [(8, 64), (3, 201), (4, 512)])
+def test_f32_error_against_64_bits(P, B_, S):
+    """Sums over K are folded every 128 values, as K parts of four stages are,
+    so that one pass rounds no more than parts do: 2.74e-7, 2.86e-7 and 2.87e-7
+    here (2.74e-7, 2.87e-7 and 2.85e-7 in parts), where folds every 256 give
+    3.00e-7, 2.95e-7 and 3.19e-7."""
+    shape = synth.TINY
+    errs = []
+    for seed in range(6):
+        w_np = synth.model_weights_np(shape, seed=20 + seed, dtype="f32")
+        model = P.Model(shape, {k: torch.from_numpy(v).to(DEV) for k, v in w_np.items()}, dtype="f32", max_pos=512)
+        toks = synth.tokens_np(21 + seed, "toks", B_ * S, shape.vocab - 1).reshape(B_, S)
+        toks[:, S // 2:] = shape.mask_id
+        lm_pos = np.arange(S // 2, S, 3, dtype=np.int32)
+        out = model.forward(torch.from_numpy(toks).to(DEV), torch.from_numpy(lm_pos).to(DEV))
+        got = out.numpy()["topk_logit"][:len(lm_pos)]
+        ref = softmax_stats(om.forward_logits(toks[:1], w_np, shape, lm_pos).reshape(-1, shape.vocab), 16).topk_logit
+        errs.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+        model.close()
+    print(f"f32 error {B_} x {S}: {np.mean(errs):.3e}", errs)
+    assert np.mean(errs) < 2.9e-7
