@@ -140,7 +140,10 @@ dllm_status dllm_model_create(const dllm_model_desc* desc, const dllm_weights* w
 void dllm_model_destroy(dllm_model* m);
 
 /* Workspace of dllm_forward for `batch` sequences of `seq` positions with
- * statistics at n_lm_pos positions of each sequence. */
+ * statistics at n_lm_pos positions of each sequence.  It serves every forward
+ * of the model whose batch, seq and n_lm_pos are none of them larger: the
+ * needs of single forwards do not grow evenly (few rows take more parts of
+ * their sums), the size returned does. */
 size_t dllm_workspace_bytes(const dllm_model* m, int32_t batch, int32_t seq, int32_t n_lm_pos);
 
 /* One denoising forward (the model call of Algorithm 1) over a batch of
@@ -196,7 +199,8 @@ dllm_status dllm_forward(dllm_model* m, const int32_t* tokens, int32_t batch, in
  *                shared sequence = the block and the masked suffix, with
  *                block_start 0).
  *   Other arguments as dllm_forward (batch 1, no kv_out).  The workspace is
- *   dllm_workspace_bytes_packed(m, shared_len, block_len, n_branch, n_lm_pos).
+ *   dllm_workspace_bytes_packed(m, shared_len, block_len, n_branch, n_lm_pos),
+ *   which serves every packed forward with none of these four larger.
  * Errors: DLLM_ESHAPE unless 1 <= n_lm_pos <= shared_len, block_len is a
  *   power of two, n_branch >= 0, 0 <= block_start, block_start + block_len <=
  *   shared_len and pos_offset + shared_len <= max_pos. */
@@ -214,7 +218,9 @@ dllm_status dllm_forward_packed(dllm_model* m, const int32_t* tokens, int32_t sh
  * logit[mask_id] = -inf (mask_id < 0: none), then H, lse, lmax, argmax and
  * top-k.  The [R][vocab] logits are never written to memory.
  *   hidden [R][d], w_lm [vocab][d], dtype of both = `dtype`.  d % 64 == 0
- *   (bf16) or d % 32 == 0 (f32). */
+ *   (bf16) or d % 32 == 0 (f32).
+ * The workspace is for R rows alone: fewer rows can need more of it (they are
+ * split into more slices of the vocabulary). */
 size_t vocab_entropy_topk_workspace_bytes(int32_t R, int32_t vocab);
 dllm_status vocab_entropy_topk(const void* hidden, const void* w_lm, int32_t R, int32_t d, int32_t vocab,
                                int32_t dtype, const float* row_scale, float scale, int32_t mask_id,

@@ -19,6 +19,9 @@ struct dllm_model {
   dllm_model_desc desc;
   const void* emb;
   const void* lm_head;
+  // Largest split-K and LM-head workspace of a forward of at most 64 (i + 1)
+  // rows: smaller launches can take more parts and need more than larger ones
+  std::vector<size_t> part_max, lm_max;
   std::vector<const void*> wqkv, wo, wgu, wdown;
   float2* rope;
   // kernel timing (dllm_profile_begin / end)
@@ -103,7 +106,8 @@ struct GemmSplits {
   size_t bytes;
 };
 
-GemmSplits plan_gemms(const dllm_model_desc& d, int M) {
+// splits as planned for M rows, bytes for `rows` of them
+GemmSplits plan_gemms(const dllm_model_desc& d, int M, int rows) {
   const int dt = d.dtype;
   auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
   const int tq = cdiv(3 * d.d_model, 256), to = cdiv(d.d_model, 256), tg = cdiv(d.d_ffn, 128);
@@ -112,9 +116,32 @@ GemmSplits plan_gemms(const dllm_model_desc& d, int M) {
   g.o = gemm_splits(GEMM_KIND_RESID, M, d.d_model, d.d_model, dt);
   g.gu = d.d_ffn % 4 ? 1 : gemm_splits(GEMM_KIND_GATEUP, M, 2 * d.d_ffn, d.d_model, dt);
   g.down = gemm_splits(GEMM_KIND_RESID, M, d.d_model, d.d_ffn, dt);
-  g.bytes = std::max(std::max(gemm_partial_bytes(M, tq, g.qkv), gemm_partial_bytes(M, to, g.o)),
-                     std::max(gemm_partial_bytes(M, tg, g.gu), gemm_partial_bytes(M, to, g.down)));
+  g.bytes = std::max(std::max(gemm_partial_bytes(rows, tq, g.qkv), gemm_partial_bytes(rows, to, g.o)),
+                     std::max(gemm_partial_bytes(rows, tg, g.gu), gemm_partial_bytes(rows, to, g.down)));
   return g;
+}
+GemmSplits plan_gemms(const dllm_model_desc& d, int M) { return plan_gemms(d, M, M); }
+
+// Row counts 64 i + 1 .. 64 i + 64 have the same tiles in every launch, and
+// parts that only get dearer with the rows (their traffic), so the first of
+// them has the most parts.
+constexpr int kEnvRows = 64;
+constexpr int kEnvKept = 1024;   // entries kept with the model (65536 rows)
+constexpr int kMaxRows = 1 << 24;   // of one forward
+size_t part_bytes_of(const dllm_model_desc& d, int i) {
+  return plan_gemms(d, kEnvRows * i + 1, kEnvRows * (i + 1)).bytes;
+}
+// largest split-K workspace of a forward of at most M rows
+size_t part_bytes_upto(const dllm_model* m, int M) {
+  const int n = (M + kEnvRows - 1) / kEnvRows;
+  size_t b = m->part_max[std::min(n, kEnvKept) - 1];
+  for (int i = kEnvKept; i < n; ++i) b = std::max(b, part_bytes_of(m->desc, i));
+  return b;
+}
+// and of its LM head over at most R rows (past the kept ones it grows with R)
+size_t lm_bytes_upto(const dllm_model* m, int R) {
+  const int n = (R + kEnvRows - 1) / kEnvRows;
+  return std::max(m->lm_max[std::min(n, kEnvKept) - 1], lmhead_workspace(m->desc.dtype, R, m->desc.vocab));
 }
 
 // packed lookahead layout of one forward (see dllm_forward_packed)
@@ -122,8 +149,11 @@ struct Packing {
   int S, b0, B, n_branch;
 };
 
-// R: LM-head rows of the call (batch * n_lm_pos, or (1 + n_branch) * n_lm_pos packed)
-FwdLayout plan_forward(const dllm_model_desc& d, int batch, int seq, int R) {
+// Regions of a forward with `lm`, `part` and `attn` bytes for the LM head's
+// partials, the split-K parts and the attention's key ranges; the others grow
+// with batch, seq and R, the LM-head rows of the call (batch * n_lm_pos, or
+// (1 + n_branch) * n_lm_pos packed).
+FwdLayout layout_forward(const dllm_model_desc& d, int batch, int seq, int R, size_t lm, size_t part, size_t attn) {
   FwdLayout L;
   const size_t T = elem_bytes(d.dtype);
   const size_t M = size_t(batch) * seq;
@@ -141,13 +171,28 @@ FwdLayout plan_forward(const dllm_model_desc& d, int batch, int seq, int R) {
   L.vt = take(size_t(batch) * d.n_heads * d.head_dim * L.vt_ld * T);
   L.f = take(M * d.d_ffn * T);
   L.hl = take(size_t(R) * d.d_model * T);
-  L.lm = take(lmhead_workspace(R, d.vocab));
+  L.lm = take(lm);
   L.lmsrc = take(size_t(R) * 8);
-  L.part = take(plan_gemms(d, int(M)).bytes);
-  const size_t attn_bytes = attn_partial_bytes(batch, d.n_heads, seq, d.head_dim);
-  L.attn = attn_bytes ? take(attn_bytes) : 0;
+  L.part = take(part);
+  L.attn = attn ? take(attn) : 0;
   L.total = off;
   return L;
+}
+
+// what one forward needs
+FwdLayout plan_forward(const dllm_model_desc& d, int batch, int seq, int R) {
+  return layout_forward(d, batch, seq, R, lmhead_workspace(d.dtype, R, d.vocab), plan_gemms(d, batch * seq).bytes,
+                        attn_partial_bytes(batch, d.n_heads, seq, d.head_dim));
+}
+
+// what it and every forward of no more sequences, positions and LM-head rows
+// needs (arguments past kMaxRows are refused by the forward)
+size_t workspace_upto(const dllm_model* m, int64_t batch, int64_t seq, int64_t R) {
+  const dllm_model_desc& d = m->desc;
+  const int b = int(std::min<int64_t>(batch, kMaxRows)), s = int(std::min<int64_t>(seq, kMaxRows)),
+            M = int(std::min<int64_t>(int64_t(b) * s, kMaxRows)), r = int(std::min<int64_t>(R, kMaxRows));
+  return layout_forward(d, b, s, r, lm_bytes_upto(m, r), part_bytes_upto(m, M),
+                        attn_partial_bytes_upto(M, d.n_heads, d.head_dim)).total;
 }
 
 }  // namespace
@@ -216,6 +261,10 @@ dllm_status dllm_model_create(const dllm_model_desc* desc, const dllm_weights* w
   m->wgu.assign(w->wgu, w->wgu + d.n_layers);
   m->wdown.assign(w->wdown, w->wdown + d.n_layers);
   m->rope = rope;
+  for (int i = 0; i < kEnvKept; ++i) {
+    m->part_max.push_back(std::max(i ? m->part_max[i - 1] : 0, part_bytes_of(d, i)));
+    m->lm_max.push_back(std::max(i ? m->lm_max[i - 1] : 0, lmhead_workspace(d.dtype, kEnvRows * (i + 1), d.vocab)));
+  }
   *out = m;
   return DLLM_OK;
 }
@@ -296,13 +345,13 @@ dllm_status dllm_mfma_ceiling(int32_t random_operands, float* tflops, dllm_strea
 
 size_t dllm_workspace_bytes(const dllm_model* m, int32_t batch, int32_t seq, int32_t n_lm_pos) {
   if (!m || batch < 1 || seq < 1 || n_lm_pos < 1) return 0;
-  return plan_forward(m->desc, batch, seq, batch * n_lm_pos).total;
+  return workspace_upto(m, batch, seq, int64_t(batch) * n_lm_pos);
 }
 
 size_t dllm_workspace_bytes_packed(const dllm_model* m, int32_t shared_len, int32_t block_len, int32_t n_branch,
                                    int32_t n_lm_pos) {
   if (!m || shared_len < 1 || block_len < 1 || n_branch < 0 || n_lm_pos < 1) return 0;
-  return plan_forward(m->desc, 1, shared_len + n_branch * block_len, (1 + n_branch) * n_lm_pos).total;
+  return workspace_upto(m, 1, int64_t(shared_len) + int64_t(n_branch) * block_len, (int64_t(1) + n_branch) * n_lm_pos);
 }
 
 namespace {
@@ -331,7 +380,7 @@ dllm_status forward_impl(dllm_model* m, const int32_t* tokens, int32_t batch, in
   if (!std::isfinite(scale)) return fail(DLLM_EINVAL, "scale is not finite");
   const size_t T = elem_bytes(d.dtype);
   const size_t M = size_t(batch) * seq;
-  if (M * std::max(d.d_model, d.d_ffn) * T >= (size_t(1) << 32) || M > (size_t(1) << 24))
+  if (M * std::max(d.d_model, d.d_ffn) * T >= (size_t(1) << 32) || M > size_t(kMaxRows))
     return fail(DLLM_ESHAPE, "batch * seq too large");
   if (kv_prefix) {
     if (!kv_prefix->k || !kv_prefix->vt) return fail(DLLM_EINVAL, "kv_prefix has a NULL array");
@@ -512,7 +561,7 @@ dllm_status dllm_forward_packed(dllm_model* m, const int32_t* tokens, int32_t sh
 
 size_t vocab_entropy_topk_workspace_bytes(int32_t R, int32_t vocab) {
   if (R < 1 || vocab < 2) return 0;
-  return lmhead_workspace(R, vocab);
+  return std::max(lmhead_workspace(DLLM_F32, R, vocab), lmhead_workspace(DLLM_BF16, R, vocab));
 }
 
 dllm_status vocab_entropy_topk(const void* hidden, const void* w_lm, int32_t R, int32_t d, int32_t vocab,
@@ -530,7 +579,7 @@ dllm_status vocab_entropy_topk(const void* hidden, const void* w_lm, int32_t R, 
     return fail(DLLM_ESHAPE, "operand exceeds 4 GiB");
   if (mask_id >= vocab) return fail(DLLM_EINVAL, "mask_id >= vocab");
   if (!std::isfinite(scale)) return fail(DLLM_EINVAL, "scale is not finite");
-  const size_t need = lmhead_workspace(R, vocab);
+  const size_t need = vocab_entropy_topk_workspace_bytes(R, vocab);
   if (ws_bytes < need) return fail(DLLM_ENOMEM, "workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
   TRY_HIP(lmhead_partials(dtype, hidden, w_lm, R, d, vocab, row_scale, nullptr, R, R, scale, mask_id, ws, s),
@@ -578,7 +627,7 @@ dllm_status vocab_entropy_topk_noalloc(const void* hidden, const void* w_lm, int
                                        int32_t dtype, const float* row_scale, float scale, int32_t mask_id,
                                        const dllm_stats* out, dllm_stream stream) {
   if (R < 1 || vocab < 2) return fail(DLLM_ESHAPE, "R %d vocab %d", R, vocab);
-  const size_t need = lmhead_workspace(R, vocab);
+  const size_t need = vocab_entropy_topk_workspace_bytes(R, vocab);
   if (need > size_t(DLLM_NOALLOC_SCRATCH_BYTES))
     return fail(DLLM_ENOMEM, "vocab_entropy_topk_noalloc: R %d x vocab %d needs %zu bytes of partials, beyond the "
                 "%zu-byte device scratch", R, vocab, need, size_t(DLLM_NOALLOC_SCRATCH_BYTES));

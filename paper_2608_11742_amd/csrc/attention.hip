@@ -567,6 +567,12 @@ size_t attn_partial_bytes(int B, int H, int Sq, int hd) {
   return size_t(kKvMaxSplits) * B * H * Sq * kv_rec(hd) * sizeof(float);
 }
 
+size_t attn_partial_bytes_upto(int rows, int H, int hd) {
+  // fewer than kKvMinWg workgroups of kQW queries
+  const int most = std::min(rows, (kKvMinWg - 1) / H * kQW);
+  return size_t(kKvMaxSplits) * H * most * kv_rec(hd) * sizeof(float);
+}
+
 hipError_t attention(int dtype, const AttnArgs& a, hipStream_t s) {
   if (dtype) return a.hd == 128 ? launch_attn<bf16_t, 128>(a, s) : launch_attn<bf16_t, 64>(a, s);
   return a.hd == 128 ? launch_attn<float, 128>(a, s) : launch_attn<float, 64>(a, s);

@@ -83,6 +83,8 @@ struct AttnArgs {
 hipError_t attention(int dtype, const AttnArgs& a, hipStream_t s);
 // workspace for the key split of an attention over B x H x Sq queries (0: never split)
 size_t attn_partial_bytes(int B, int H, int Sq, int hd);
+// the largest of them over any B and Sq of at most `rows` queries in all
+size_t attn_partial_bytes_upto(int rows, int H, int hd);
 
 // LM-head rows of a packed lookahead forward: (1 + n_branch) * n_lm rows, the
 // shared sequence's then each branch's; row[] is the packed row each reads,
@@ -103,7 +105,7 @@ struct StatsOut {
   float* topk_logit;
   int k;
 };
-size_t lmhead_workspace(int R, int V);
+size_t lmhead_workspace(int dtype, int R, int V);
 // Pass 1 writes per-slice partial statistics to ws; pass 2 merges them into out.
 // row_scale (nullable) is indexed by rs_idx[row % rs_n] clamped to [0, rs_lim) (or row % rs_n without rs_idx)
 hipError_t lmhead_partials(int dtype, const void* h, const void* w, int R, int d, int V, const float* row_scale,

@@ -529,10 +529,8 @@ Partials carve(void* ws, int R, int P) {
 
 }  // namespace
 
-size_t lmhead_workspace(int R, int V) {
-  size_t P = 0;
-  for (int dtype = 0; dtype < 2; ++dtype) P = std::max(P, size_t(partials_per_row(lm_tile(dtype, R, V), R, V)));
-  return size_t(R) * P * (3 + 2 * kK) * 4 + 256;
+size_t lmhead_workspace(int dtype, int R, int V) {
+  return size_t(R) * partials_per_row(lm_tile(dtype, R, V), R, V) * (3 + 2 * kK) * 4 + 256;
 }
 
 hipError_t lmhead_partials(int dtype, const void* h, const void* w, int R, int d, int V, const float* row_scale,

@@ -244,3 +244,32 @@ def test_f32_error_against_64_bits(P, B_, S):
         model.close()
     print(f"f32 error {B_} x {S}: {np.mean(errs):.3e}", errs)
     assert np.mean(errs) < 2.9e-7
+
+
+# one workspace, sized for the longest forward of a decode, serves the shorter
+# ones: few rows take more K parts and smaller LM head tiles than many
+def test_workspace_serves_every_smaller_forward(P):
+    shape = ModelShape(n_layers=1, d_model=2048, n_heads=32, head_dim=64, d_ffn=5632, vocab=4000)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    dims = {"emb": (4000, 2048), "lm_head": (4000, 2048), "layers.0.wqkv": (6144, 2048), "layers.0.wo": (2048, 2048),
+            "layers.0.wgu": (11264, 2048), "layers.0.wdown": (2048, 5632)}
+    w = {k: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0, 0.02, generator=gen) for k, s in dims.items()}
+    model = P.Model(shape, w, dtype="bf16", max_pos=1024)
+    need = lambda b, s, n: P.dllm_workspace_bytes(model.handle, b, s, n)
+    for b, n in [(1, 300), (1, 1), (3, 64)]:
+        sizes = [need(b, s, min(n, s)) for s in range(1, 1025)]
+        assert sizes == sorted(sizes)
+    packed = [P.dllm_workspace_bytes_packed(model.handle, 256, 32, n, 32) for n in range(16)]
+    assert packed == sorted(packed)
+    assert need(1 << 20, 1 << 20, 1 << 20) > 0      # past every limit: an answer all the same
+    ws = torch.empty(need(1, 1024, 300), dtype=torch.uint8, device=DEV)
+    for s in (17, 33, 129, 257, 300, 321, 513, 769, 1023):
+        n = min(s, 300)
+        toks = torch.from_numpy(synth.tokens_np(s, "t", s, 3999)).to(DEV)[None]
+        lm = torch.arange(n, dtype=torch.int32, device=DEV)
+        out, own = P.Stats(n, 16, device=DEV), P.Stats(n, 16, device=DEV)
+        P.dllm_forward(model.handle, toks, lm, out, ws)
+        P.dllm_forward(model.handle, toks, lm, own, torch.empty(need(1, s, n), dtype=torch.uint8, device=DEV))
+        for k, v in out.numpy().items():
+            assert np.array_equal(v, own.numpy()[k]), (s, k)
+    model.close()
