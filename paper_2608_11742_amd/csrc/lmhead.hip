@@ -83,10 +83,12 @@ int slices_for(int bm, int R, int V) {
 
 // Row tile of an LM head over R rows and V vocabulary entries.
 int lm_tile(int dtype, int R, int V) {
+  // 2 partials a row and slice instead of 4; first, so that the products of
+  // tile counts below stay within int
+  if (R > 32768) return 256;
   const bool few = cdiv(R, 128) * cdiv(V, 256) < kTargetWg / 2;   // 128 x 256 tiles would leave half the CUs idle
   if (R <= 64 || few) return 64;
   if (R <= 128) return 128;
-  if (R > 32768) return 256;   // 2 partials a row and slice instead of 4
   const int t128 = tile_times(128, R, V, slices_for(128, R, V));
   // the fp32 matrix cores bound every tile: two 64 x 128 ones share a CU, so
   // each takes half the time of a 128 x 256 one (352 rows, vocabulary 32000: 3

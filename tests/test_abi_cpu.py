@@ -119,6 +119,14 @@ def test_vocab_entropy_topk_validation(abi):
     assert "workspace" in _err(lib)
 
 
+def test_vocab_entropy_topk_workspace_of_many_rows(abi):
+    """Past 32768 rows a row takes two partials of 140 bytes a vocabulary slice,
+    whatever the product of the tile counts."""
+    _, lib = abi
+    for R, V in [(1 << 17, 1000), (1 << 22, 1 << 25), (1 << 24, 1 << 24)]:
+        assert lib.vocab_entropy_topk_workspace_bytes(R, V) == R * 2 * 140 + 256
+
+
 def test_scheduler_validation(abi):
     _abi, lib = abi
     fake = C.c_void_p(0x4000)
