@@ -295,7 +295,7 @@ __device__ void commit_compact(int32_t* __restrict__ tokens, int seq, int32_t* _
   // (new index), kT rows at a time from ballots; one thread walking the rows
   // took 25 us for 256 of them
   int cs = 0, ks = 0;
-  bool outside = false;
+  bool ordered = true;   // positions ascend within the sequence, as they should: no two rows write one token
   for (int r0 = 0; r0 < n_m; r0 += kT) {
     const int j = r0 + tid;
     const bool c = j < n_m && sel[j], keep = j < n_m && j != s_drop && !sel[j];
@@ -311,22 +311,24 @@ __device__ void commit_compact(int32_t* __restrict__ tokens, int seq, int32_t* _
       cs += cnt[0][w];
       ks += cnt[1][w];
     }
-    if (c) {
-      const int p = m_pos[j];
-      committed[s_nc + ci] = p;
-      outside = outside || p < 0 || p >= seq;
-      if (p >= 0 && p < seq) tokens[p] = src.argmax[j];
+    if (j < n_m) {
+      const int p = m_pos[j], before = j > 0 ? m_pos[j - 1] : -1;
+      ordered = ordered && p > before && p < seq;
+      if (c) {
+        committed[s_nc + ci] = p;
+        if (p >= 0 && p < seq) tokens[p] = src.argmax[j];
+      }
+      pre[j] = keep ? ki : -1;
     }
-    if (j < n_m) pre[j] = keep ? ki : -1;
     __syncthreads();
   }
   if (tid == 0) {
     *n_m_out = ks;
     *n_committed = s_nc + cs;
   }
-  // positions outside the sequence are clamped; several rows may then write
-  // one token, in row order
-  if (__syncthreads_or(outside) && tid == 0)
+  // positions outside the sequence are clamped, and others may repeat: where
+  // several rows write one token, the last of them in row order stays
+  if (__syncthreads_or(!ordered) && tid == 0)
     for (int j = 0; j < n_m; ++j)
       if (sel[j]) tokens[min(max(m_pos[j], 0), seq - 1)] = src.argmax[j];
   __syncthreads();

@@ -113,6 +113,29 @@ def test_commit_rows(P, n_m, shift):
         assert (got[n][:keep.sum()] == v[keep]).all(), n
 
 
+@pytest.mark.parametrize("n_m", [2, 64, 300, 1024])
+@pytest.mark.parametrize("order", ["pairs", "shuffled", "all"])
+def test_commit_of_repeated_positions(P, n_m, order):
+    """Several rows at one position: committed[] lists them all, and the last
+    row's token stays, whichever waves the rows are in."""
+    rng = np.random.default_rng(n_m)
+    seq = n_m + 3
+    pos = {"pairs": np.arange(n_m) // 2, "shuffled": rng.permutation(n_m) // 3, "all": np.full(n_m, 2)}[order]
+    pos = pos.astype(np.int32)
+    base = P.Stats(n_m, 4, device=DEV).fill_(0.0)
+    ids = rng.permutation(9000)[:n_m].astype(np.int32)
+    base.argmax.copy_(torch.from_numpy(ids))
+    tokens = np.full(seq, -1, np.int32)
+    t, m = torch.from_numpy(tokens).to(DEV), torch.from_numpy(pos).to(DEV)
+    one = lambda n: torch.full((n,), -7, dtype=torch.int32, device=DEV)
+    n_out, com, n_com = one(1), one(n_m), one(1)
+    P.rps_commit(t, m, n_m, base, 0.5, n_out, com, n_com)
+    for j in range(n_m):
+        tokens[pos[j]] = ids[j]
+    assert n_out.item() == 0 and n_com.item() == n_m
+    assert (com.cpu().numpy() == pos).all() and (t.cpu().numpy() == tokens).all()
+
+
 # bf16 projections: rows at the edges of the 64-, 128- and 256-row tiles and of
 # the ranges that choose between them, an FFN whose last tile is partly filled
 @pytest.mark.parametrize("hd", [64, 128])
