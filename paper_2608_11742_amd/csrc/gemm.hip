@@ -128,15 +128,9 @@ GemmPlan plan_bf16(int kind, int M, int N, int K) {
     }
     return best;
   }
-  // A QKV projection of K < 1024 over few rows stays in two or more parts: the
-  // parity bounds of the small bf16 models are tight enough to tell one order
-  // of its fp32 sums from another (d 512, 448 rows, 8 layers: 520 us, 473 in
-  // one pass).
-  if (kind == GEMM_KIND_QKV && M <= 512 && stages < 16)
-    if (const int p = fill(cdiv(M, Mid::BM) * cdiv(N, Mid::BN), 256); p > 1 && N % Mid::BN == 0) return {T_MID, p};
   // one pass with the epilogue fused
   for (Tile t : {T_BIG, T_MID, T_128x192, T_128x128}) offer(t, 1, 0.0);
-  if (kind == GEMM_KIND_QKV && M <= 512 && N % Mid::BN == 0)
+  if (kind == GEMM_KIND_QKV && M <= 512)   // N = 3 d is whole 192-column tiles: d is a multiple of 256
     // 256 x 192 parts and a launch that sums them, 5 us and a read of each part
     // (d 4096: 512 rows in one pass gain 2.5 us a layer, 320 and 400 rows lose 1)
     for (int p = 2; p <= 16 && stages / p >= 4; p *= 2) offer(T_MID, p, 5.0 + parts_us(M, N, p));
