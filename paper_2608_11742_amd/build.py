@@ -30,7 +30,7 @@ def sources():
 # The LM head with 256-row tiles keeps a few loop-invariant scalars (row-scale
 # indexing, descriptor words) in scratch: they are stored once and reloaded
 # once per 256 x 256 x d tile, outside the MFMA loop, which spills nothing.
-SCRATCH_ALLOWED = {"lmhead_kernelINS_6bf16_tELi256E": 64, "lmhead_kernelIfLi256E": 64}
+SCRATCH_ALLOWED = {"lmhead_kernelINS_6bf16_tELi256E": 32, "lmhead_kernelIfLi256E": 48}
 
 
 def _scratch_users(remarks: str):

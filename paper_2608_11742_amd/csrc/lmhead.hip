@@ -241,7 +241,7 @@ __global__ __launch_bounds__((LmCfg<T, BM>::kThreads), (LmCfg<T, BM>::kMinBlocks
         for (int ni = 0; ni < TM::kFN; ++ni) {
           // (transposed blocks) row 16 mi + lane % 16, columns 16 ni + 4 (lane / 16) + 0..3
           const int r = wm * TM::kWTM + mi * 16 + (lane & 15);
-          const int c = wn * TM::kWTN + ni * 16 + 4 * (lane >> 4) - pass * Cfg::kPassCols;
+          const unsigned c = wn * TM::kWTN + ni * 16 + 4 * (lane >> 4) - pass * Cfg::kPassCols;   // >= 0
           *reinterpret_cast<f32x4*>(smem + r * kRowStride + (c / kSegCols) * kSegStride + (c % kSegCols) * 4) =
               acc[mi][ni];
         }
