@@ -158,6 +158,7 @@ struct EpiParams {
 template <typename T, class Cfg, class TM>
 __device__ __forceinline__ void swiglu_store(const f32x4 (&acc)[TM::kFM][TM::kFN], int m0, int tn, int M,
                                              const EpiParams& ep) {
+  static_assert(Elem<T>::bytes == 2, "fp32 takes gemm_direct_kernel");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   T* out = reinterpret_cast<T*>(ep.out);
@@ -180,11 +181,8 @@ __device__ __forceinline__ void swiglu_store(const f32x4 (&acc)[TM::kFM][TM::kFN
 #pragma unroll
       for (int n = 0; n < kNG; ++n) {
         T* dst = out + size_t(r0 + 16 * m) * ep.F + j0 + 16 * n;
-        if constexpr (Elem<T>::bytes == 2)
-          *reinterpret_cast<u32x2*>(dst) =
-              u32x2{pack_bf16x2(v[m][n][0], v[m][n][1]), pack_bf16x2(v[m][n][2], v[m][n][3])};
-        else
-          *reinterpret_cast<f32x4*>(dst) = f32x4{v[m][n][0], v[m][n][1], v[m][n][2], v[m][n][3]};
+        *reinterpret_cast<u32x2*>(dst) =
+            u32x2{pack_bf16x2(v[m][n][0], v[m][n][1]), pack_bf16x2(v[m][n][2], v[m][n][3])};
       }
   } else {
 #pragma unroll
@@ -336,40 +334,36 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
     // both the MFMA-layout writes and the row reads are conflict-free; then
     // every lane reads 16 bytes of x per access, all loads first (clamped
     // into the matrix) and the guarded stores after them.
-    static_assert((TM::kWTM % 64 == 0 || TM::kWTM == 32) && TM::kWTN == 128, "resid epilogue tiling");
-    constexpr int RG = TM::kWTM >= 64 ? 64 : TM::kWTM;   // rows per staged group
-    static_assert(TM::kWaves * RG * 64 * 4 <= TM::kSmem, "staging inside the ring");
-    uint8_t* st = smem + wave * (RG * 64 * 4);
+    static_assert(TM::kWTM == 64 && TM::kWTN == 128, "resid epilogue tiling");
+    static_assert(TM::kWaves * 64 * 64 * 4 <= TM::kSmem, "staging inside the ring");
+    uint8_t* st = smem + wave * (64 * 64 * 4);
     auto slot_of = [](int r, int c4) { return r * 256 + (((c4 ^ (r & 15))) << 4); };
+    const int r0 = m0 + wm * TM::kWTM;
 #pragma unroll
-    for (int g = 0; g < TM::kWTM / RG; ++g) {   // row groups of the wave tile
-      const int r0 = m0 + wm * TM::kWTM + RG * g;
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int m = 0; m < TM::kFM; ++m)
 #pragma unroll
-        for (int m = 0; m < RG / 16; ++m)
+        for (int nn = 0; nn < 4; ++nn)
 #pragma unroll
-          for (int nn = 0; nn < 4; ++nn)
+          for (int i = 0; i < 4; ++i) {
+            const int r = m * 16 + 4 * (lane >> 4) + i, c = nn * 16 + lc;
+            *reinterpret_cast<float*>(st + slot_of(r, c >> 2) + (c & 3) * 4) = acc[m][4 * h + nn][i];
+          }
+      const int c0 = tn * Cfg::BN + wn * TM::kWTN + 64 * h;
+      f32x4 xv[16];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int r = m * 16 + 4 * (lane >> 4) + i, c = nn * 16 + lc;
-              *reinterpret_cast<float*>(st + slot_of(r, c >> 2) + (c & 3) * 4) = acc[(RG / 16) * g + m][4 * h + nn][i];
-            }
-        const int c0 = tn * Cfg::BN + wn * TM::kWTN + 64 * h;
-        f32x4 xv[RG / 4];
+      for (int j = 0; j < 16; ++j) {
+        const int q = lane + 64 * j, r = q >> 4, c4 = q & 15;
+        const int row = min(r0 + r, M - 1), col = min(c0 + 4 * c4, N - 4);
+        xv[j] = *reinterpret_cast<const f32x4*>(ep.x + size_t(row) * ep.ldx + col);
+      }
 #pragma unroll
-        for (int j = 0; j < RG / 4; ++j) {
-          const int q = lane + 64 * j, r = q >> 4, c4 = q & 15;
-          const int row = min(r0 + r, M - 1), col = min(c0 + 4 * c4, N - 4);
-          xv[j] = *reinterpret_cast<const f32x4*>(ep.x + size_t(row) * ep.ldx + col);
-        }
-#pragma unroll
-        for (int j = 0; j < RG / 4; ++j) {
-          const int q = lane + 64 * j, r = q >> 4, c4 = q & 15;
-          const int row = r0 + r, col = c0 + 4 * c4;
-          const f32x4 a = *reinterpret_cast<const f32x4*>(st + slot_of(r, c4));
-          if (row < M && col < N) *reinterpret_cast<f32x4*>(ep.x + size_t(row) * ep.ldx + col) = xv[j] + a;
-        }
+      for (int j = 0; j < 16; ++j) {
+        const int q = lane + 64 * j, r = q >> 4, c4 = q & 15;
+        const int row = r0 + r, col = c0 + 4 * c4;
+        const f32x4 a = *reinterpret_cast<const f32x4*>(st + slot_of(r, c4));
+        if (row < M && col < N) *reinterpret_cast<f32x4*>(ep.x + size_t(row) * ep.ldx + col) = xv[j] + a;
       }
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -395,20 +389,18 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
           const int pos = o.pos_offset + (o.pack_B && r >= o.pack_S ? o.pack_b0 + ((r - o.pack_S) & (o.pack_B - 1)) : r);
 #pragma unroll
           for (int n = 0; n < TM::kFN; ++n) {
-            if constexpr (true) {
-              if (((n * 16) % hd) >= half) continue;
-              const int dim = (cin0 + n * 16 + lc) % hd;
-              const float2 cs = o.rope[size_t(pos) * half + dim];
-              const float x1 = acc[m][n][i], x2 = acc[m][n + pair][i];
-              acc[m][n][i] = x1 * cs.x - x2 * cs.y;
-              acc[m][n + pair][i] = x1 * cs.y + x2 * cs.x;
-            }
+            if (((n * 16) % hd) >= half) continue;
+            const int dim = (cin0 + n * 16 + lc) % hd;
+            const float2 cs = o.rope[size_t(pos) * half + dim];
+            const float x1 = acc[m][n][i], x2 = acc[m][n + pair][i];
+            acc[m][n][i] = x1 * cs.x - x2 * cs.y;
+            acc[m][n + pair][i] = x1 * cs.y + x2 * cs.x;
           }
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    static_assert(Elem<T>::bytes == 2, "fp32 takes gemm_direct_kernel");
+    static_assert(Elem<T>::bytes == 2 && TM::kWTM == 64, "fp32 and other tiles take gemm_direct_kernel");
     {
       const int r0 = m0 + wm * TM::kWTM;
       if (which < 2) {
@@ -451,32 +443,26 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_kernel(co
         // in slot c ^ (d % 8)), and written back with 16 bytes per lane, 8
         // lanes per whole 128-byte V^T row; other tiles store the 8-byte
         // pieces straight from registers.
-        bool staged = false;
-        if constexpr (TM::kWTM == 64) {
-          static_assert(TM::kWaves * 64 * 128 * 2 <= TM::kSmem, "v staging inside the ring");
-          if (o.seq % 64 == 0 && r0 + 64 <= M && o.vt_ld % 8 == 0) {
-            uint8_t* st = smem + wave * (64 * 128 * 2);
-            auto voff = [](int d, int p) { return d * 128 + (((p >> 3) ^ (d & 7)) << 4) + (p & 7) * 2; };
+        static_assert(TM::kWaves * 64 * 128 * 2 <= TM::kSmem, "v staging inside the ring");
+        uint16_t* vt = reinterpret_cast<uint16_t*>(o.vt);
+        if (o.seq % 64 == 0 && r0 + 64 <= M && o.vt_ld % 8 == 0) {
+          uint8_t* st = smem + wave * (64 * 128 * 2);
+          auto voff = [](int d, int p) { return d * 128 + (((p >> 3) ^ (d & 7)) << 4) + (p & 7) * 2; };
 #pragma unroll
-            for (int m = 0; m < TM::kFM; ++m)
+          for (int m = 0; m < TM::kFM; ++m)
 #pragma unroll
-              for (int n = 0; n < TM::kFN; ++n)
-                *reinterpret_cast<u32x2*>(st + voff(n * 16 + lc, m * 16 + 4 * (lane >> 4))) =
-                    u32x2{pack_vt2(acc[m][n][0], acc[m][n][1]), pack_vt2(acc[m][n][2], acc[m][n][3])};
-            const int b = r0 / o.seq, sp0 = r0 - b * o.seq;
-            uint16_t* vt = reinterpret_cast<uint16_t*>(o.vt);
+            for (int n = 0; n < TM::kFN; ++n)
+              *reinterpret_cast<u32x2*>(st + voff(n * 16 + lc, m * 16 + 4 * (lane >> 4))) =
+                  u32x2{pack_vt2(acc[m][n][0], acc[m][n][1]), pack_vt2(acc[m][n][2], acc[m][n][3])};
+          const int b = r0 / o.seq, sp0 = r0 - b * o.seq;
 #pragma unroll
-            for (int it = 0; it < 128 * 8 / 64; ++it) {
-              const int q = lane + 64 * it, d = q >> 3, c = q & 7;
-              const int cin = cin0 + d, h = cin / hd, dim = cin % hd;
-              *reinterpret_cast<u32x4*>(vt + (size_t(b * o.H + h) * hd + dim) * o.vt_ld + sp0 + c * 8) =
-                  *reinterpret_cast<const u32x4*>(st + d * 128 + ((c ^ (d & 7)) << 4));
-            }
-            staged = true;
+          for (int it = 0; it < 128 * 8 / 64; ++it) {
+            const int q = lane + 64 * it, d = q >> 3, c = q & 7;
+            const int cin = cin0 + d, h = cin / hd, dim = cin % hd;
+            *reinterpret_cast<u32x4*>(vt + (size_t(b * o.H + h) * hd + dim) * o.vt_ld + sp0 + c * 8) =
+                *reinterpret_cast<const u32x4*>(st + d * 128 + ((c ^ (d & 7)) << 4));
           }
-        }
-        if (!staged) {
-          uint16_t* vt = reinterpret_cast<uint16_t*>(o.vt);
+        } else {
           const bool vec4 = (o.seq % 4) == 0 && (o.vt_ld % 4) == 0;
 #pragma unroll
           for (int m = 0; m < TM::kFM; ++m) {
@@ -545,7 +531,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kMinBlocks) void gemm_swiglu_pe
   }
 }
 
-// ---------------------------------------------------------------- fp32 projections
+// ---------------------------------------------------------------- projections with a register epilogue
 
 // Tiles of gemm_direct_kernel.
 template <typename T_, int BM_, int BN_, int WM_, int WN_, int MIN_BLOCKS, bool EARLY, int FOLD = 0>
@@ -569,7 +555,11 @@ struct DirectCfg {
 // 7.13e-7.  Folding takes 2% of the time, twice as often 0.3% more.
 using F32Cfg = DirectCfg<float, 64, 64, 4, 1, 4, false, 4>;
 // bf16 tiles, 8 (64 x 128: 4) waves, early-release schedule; plan_bf16 says
-// where each is used
+// where each is used.  256 x 192 serves one-pass QKV alone, whose rotary pairs
+// gemm_kernel cannot keep in a wave of 96 columns: gate/up and the QKV parts
+// run on the same tile in gemm_kernel (Mid), where their stores are faster
+// (forwards of 272-512 rows, d 4096, take 1.0-1.3% longer with this one, of
+// 130-256 rows 0.4-1.9%).
 using D256x192 = DirectCfg<bf16_t, 256, 192, 4, 2, 2, true>;
 using D128x192 = DirectCfg<bf16_t, 128, 192, 4, 2, 2, true>;
 using D128x128 = DirectCfg<bf16_t, 128, 128, 4, 2, 2, true>;
