@@ -434,7 +434,8 @@ __global__ __launch_bounds__(kT) void commit_kernel(int32_t* __restrict__ tokens
           if (better(pm, j, bv, bi)) { bv = pm; bi = j; }
         }
       block_argmax(bv, bi, red_v, red_i);
-      if (tid == 0) sel[bi] = 1;
+      // no confidence at all (every one a NaN): the first row left
+      if (tid == 0) sel[bi < n_m ? bi : drop == 0 ? 1 : 0] = 1;
       n_sel = 1;
       __syncthreads();
     }

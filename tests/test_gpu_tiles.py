@@ -113,6 +113,17 @@ def test_commit_rows(P, n_m, shift):
         assert (got[n][:keep.sum()] == v[keep]).all(), n
 
 
+def test_commit_without_any_confidence(P):
+    """Statistics of a model gone to NaN: the first row commits, so that a decode ends."""
+    base = P.Stats(70, 4, device=DEV).fill_(float("nan"))
+    base.argmax.copy_(torch.arange(70, dtype=torch.int32))
+    t, m = torch.zeros(80, dtype=torch.int32, device=DEV), torch.arange(5, 75, dtype=torch.int32, device=DEV)
+    n_out, com, n_com = (torch.zeros(n, dtype=torch.int32, device=DEV) for n in (1, 70, 1))
+    P.rps_commit(t, m, 70, base, 0.9, n_out, com, n_com)
+    assert n_out.item() == 69 and n_com.item() == 1 and com[0].item() == 5
+    assert (m[:69].cpu() == torch.arange(6, 75)).all()
+
+
 @pytest.mark.parametrize("n_m", [2, 64, 300, 1024])
 @pytest.mark.parametrize("order", ["pairs", "shuffled", "all"])
 def test_commit_of_repeated_positions(P, n_m, order):
