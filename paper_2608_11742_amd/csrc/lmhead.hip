@@ -12,7 +12,8 @@
 // Pass 2 (merge_kernel): one workgroup per row merges all partials:
 //   M = max m_p, S = sum s_p e^(m_p - M), T = sum e^(m_p - M) (t_p + (m_p - M) s_p)
 //   lse = M + log S, H = log S - T / S, lmax = M,
-// and a 64-way merge of the sorted partial top-16 lists.
+// and the top 16 of the partials' lists: the entries no worse than a bound
+// that 16 of the lists' heads reach, sorted.
 #include <algorithm>
 #include <type_traits>
 
@@ -460,8 +461,11 @@ __global__ __launch_bounds__(512) void merge_kernel(Partials part, int R, StatsO
   S = red_s[0];
   Tt = red_t[0];
   for (int w = 1; w < W; ++w) { S += red_s[w]; Tt += red_t[w]; }
-  // sort the candidates (or, where ties filled the buffer, every entry): the
-  // ids are unique, so the order does not depend on how they were gathered
+  // Sort the candidates: the ids are unique, so the order does not depend on
+  // how they were gathered.  Or sort every entry, where the candidates
+  // overflow the buffer: with more than four waves the bound is the 16th best
+  // of pairs of heads, so up to 31 threads' lists can reach it, and past 1024
+  // partials a thread has up to four lists of 16.
   const bool all = n_cand > kCap;
   const int n = all ? part.P * kK : n_cand;
   auto entry = [&](int e, float& v, int& i) {

@@ -62,8 +62,9 @@ def test_lm_head_tiles(P, dtype, R, d, V):
 
 @pytest.mark.parametrize("R,V,k", [(2, 40000, 16), (70, 33000, 5), (1, 12, 16)])
 def test_lm_head_of_equal_logits(P, R, V, k):
-    """Ties everywhere: the ids ascend, and every partial's list reaches the
-    merge's bound.  With fewer tokens than ranks the rest stay empty."""
+    """Ties everywhere: the ids ascend, and the merge's bound, which breaks
+    ties by id, keeps few of the lists.  With fewer tokens than ranks the rest
+    stay empty."""
     out = P.Stats(R, k, device=DEV).fill_(float("nan"))
     ws = torch.empty(P.vocab_entropy_topk_workspace_bytes(R, V), dtype=torch.uint8, device=DEV)
     P.vocab_entropy_topk(torch.zeros(R, 64, dtype=torch.bfloat16, device=DEV),
@@ -73,6 +74,31 @@ def test_lm_head_of_equal_logits(P, R, V, k):
     assert (got["topk_id"][:, :len(want)] == want).all() and (got["topk_logit"][:, :len(want)] == 0).all()
     assert np.isneginf(got["topk_logit"][:, len(want):]).all()
     assert (got["argmax"] == 0).all() and np.allclose(got["H"], np.log(V - 1), atol=1e-4)
+
+
+def test_lm_head_merge_of_more_candidates_than_its_buffer(P):
+    """2048 partials of 32 tokens, thread t of the merge takes t, t + 512, ...
+    Fifteen threads of its wave 0 and of its wave 4 see one high logit in every
+    token they hold, the sixteenth of each a lower one, which is the bound:
+    30 x 4 lists of 16 reach it, 1920 candidates and more for a buffer of 1024.
+    The top 16 are spread over the lists."""
+    V, n = 65536, 16
+    part = np.arange(V) // 32 % 512
+    val = np.zeros(V, np.float32)
+    val[np.isin(part, np.r_[0:15, 256:271])] = 2.0
+    val[part == 15], val[part == 271] = 1.0, 0.5
+    top = np.array([(512 * (j % 4) + (j % 15) + 256 * (j % 2)) * 32 + 3 * j % 32 for j in range(n)])
+    val[top] = 2.5 + 0.125 * np.arange(n)
+    w = torch.zeros(V, 64, dtype=torch.bfloat16, device=DEV)
+    w[:, 0] = torch.from_numpy(val).to(DEV)
+    h = torch.zeros(2, 64, dtype=torch.bfloat16, device=DEV)
+    h[0, 0], h[1, 0] = 1.0, 2.0
+    out = P.Stats(2, 16, device=DEV).fill_(float("nan"))
+    ws = torch.full((P.vocab_entropy_topk_workspace_bytes(2, V),), 255, dtype=torch.uint8, device=DEV)
+    P.vocab_entropy_topk(h, w, out, ws)
+    got = out.numpy()
+    assert (got["topk_id"] == top[::-1]).all() and (got["argmax"] == top[-1]).all()
+    print(compare_stats(got, softmax_stats(np.stack([val, 2 * val]).astype(np.float64), 16), 1e-4, label="merge"))
 
 
 # scheduler: rows one below, at and one above the commit kernel's 256 threads
@@ -111,6 +137,52 @@ def test_commit_rows(P, n_m, shift):
     got = base.numpy()
     for n, v in {**f, **i}.items():
         assert (got[n][:keep.sum()] == v[keep]).all(), n
+
+
+# a decision to commit: its pivot's row goes, its token stands, and the rule and
+# the rows that are kept are the winning branch's
+@pytest.mark.parametrize("n_m", [2, 255, 256, 257, 1000, 1024])
+@pytest.mark.parametrize("where", ["first", "middle", "last"])
+def test_commit_of_a_pivot(P, n_m, where):
+    from paper_2608_11742_amd._abi import RpsDecision
+    rng = np.random.default_rng(n_m)
+    seq, k, nb = n_m + 7, 4, 3
+    row = {"first": 0, "middle": n_m // 2, "last": n_m - 1}[where]
+    pos = np.arange(7, seq, dtype=np.int32)
+    base, br = P.Stats(n_m, k, device=DEV).fill_(0.0), P.Stats((1 + nb) * n_m, k, device=DEV)
+    f = {n: rng.normal(size=getattr(br, n).shape).astype(np.float32) for n in ("H", "lse", "lmax", "topk_logit")}
+    sure = rng.random((1 + nb) * n_m) < 0.4
+    f["lmax"] = f["lse"] - np.where(sure, np.float32(0.05), np.float32(1.0) + np.abs(f["lmax"]))
+    i = {n: rng.integers(0, 9000, getattr(br, n).shape).astype(np.int32) for n in ("argmax", "topk_id")}
+    for n, v in {**f, **i}.items():
+        getattr(br, n).copy_(torch.from_numpy(v))
+    branch, offset = 2, 1
+    win = slice((offset + branch) * n_m, (offset + branch + 1) * n_m)
+    dec = P.new_decision(DEV)
+    dec.copy_(torch.frombuffer(bytearray(bytes(RpsDecision(1, branch, row, int(pos[row]), 8999, 0.5, 0.1, n_m))),
+                               dtype=torch.uint8))
+    tokens = rng.integers(0, 8000, seq).astype(np.int32)
+    t, m = torch.from_numpy(tokens).to(DEV), torch.from_numpy(pos).to(DEV)
+    one = lambda n: torch.full((n,), -7, dtype=torch.int32, device=DEV)
+    n_out, com, n_com = one(1), one(n_m), one(1)
+    P.rps_commit(t, m, n_m, base, 0.9, n_out, com, n_com, dec=dec, branches=br, branch_offset=offset)
+    conf = np.exp((f["lmax"][win] - f["lse"][win]).astype(np.float64))
+    conf[row] = -1.0
+    sel = conf >= 0.9
+    if not sel.any():
+        sel[np.argmax(conf)] = True
+    want = tokens.copy()
+    want[pos[row]] = 8999
+    want[pos[sel]] = i["argmax"][win][sel]
+    keep = ~sel
+    keep[row] = False
+    n = keep.sum()
+    assert n_out.item() == n and n_com.item() == 1 + sel.sum()
+    assert (com.cpu().numpy()[:1 + sel.sum()] == np.concatenate([pos[row:row + 1], pos[sel]])).all()
+    assert (t.cpu().numpy() == want).all() and (m.cpu().numpy()[:n] == pos[keep]).all()
+    got = base.numpy()
+    for name, v in {**f, **i}.items():
+        assert (got[name][:n] == v[win][keep]).all(), name
 
 
 def test_commit_without_any_confidence(P):
@@ -167,6 +239,28 @@ def test_forward_bf16_row_tiles(P, hd, B_, S):
             -1, shape.vocab), 16)
         print(compare_stats({k: v[b * n:(b + 1) * n] for k, v in got.items()}, ref, 2e-2, max_exceptions=2,
                             id_ranks=4, label=f"bf16 hd {hd} {B_} x {S} seq {b}"))
+    model.close()
+
+
+# the smallest bf16 models: K too short for parts, so that up to 64 rows take
+# every unsplit 64 x 128 kernel; 65-128 rows with a small FFN, whose gate/up
+# runs in parts of 128 x 128 tiles
+@pytest.mark.parametrize("d,hd,F,S", [(256, 64, 256, 1), (256, 64, 256, 33), (256, 64, 256, 64), (256, 128, 256, 1),
+                                      (256, 128, 256, 33), (256, 128, 256, 64), (512, 64, 640, 65),
+                                      (512, 128, 640, 128)])
+def test_forward_bf16_small_models(P, d, hd, F, S):
+    shape = ModelShape(n_layers=1, d_model=d, n_heads=d // hd, head_dim=hd, d_ffn=F, vocab=600)
+    w_np = synth.model_weights_np(shape, seed=7, dtype="bf16")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV).bfloat16() for k, v in w_np.items()}, dtype="bf16",
+                    max_pos=128)
+    toks = synth.tokens_np(S, "toks", S, shape.vocab - 1)[None]
+    toks[:, S // 2 + 1:] = shape.mask_id
+    lm_pos = np.unique(np.array([0, S // 3, S // 2, S - 1], dtype=np.int32))
+    out = model.forward(torch.from_numpy(toks).to(DEV), torch.from_numpy(lm_pos).to(DEV), scale=2.0)
+    torch.cuda.synchronize()
+    ref = softmax_stats(om.forward_logits(toks, w_np, shape, lm_pos, scale=2.0, mirror=True).reshape(-1, shape.vocab),
+                        16)
+    print(compare_stats(out.numpy(), ref, 2e-2, max_exceptions=2, id_ranks=4, label=f"bf16 d {d} hd {hd} x {S}"))
     model.close()
 
 
