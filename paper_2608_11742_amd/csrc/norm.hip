@@ -1,5 +1,7 @@
 // Row-wise kernels of the forward: embedding gather with the first RMSNorm,
 // RMSNorm (optionally gathering rows) and the prefix-cache writer.
+#include <type_traits>
+
 #include "kernels.h"
 #include "common.h"
 
@@ -19,8 +21,12 @@ __device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f3
 
 constexpr int kNormChunks = 8;   // 16-byte chunks per thread held in registers: d <= 8192
 // resid_rmsnorm: 1024 threads a row, so that each walks the partials of one or
-// two chunks with every load in flight (512 rows of 8 parts, d 4096: a 265 us
-// layer gains 1.3 us over 256 threads a row, 1536 rows 4)
+// two chunks (512 rows of 8 parts, d 4096: a 265 us layer gains 1.3 us over 256
+// threads a row, 1536 rows 4; up to d 2048 part of the threads have no chunk).
+// The loads of 8, then 4, then 2 parts are in flight together: with 2 and 4
+// parts loaded one after the other a launch took 11.5 us instead of 10.6 (1536
+// rows, d 512), 9.8 instead of 9.3 (700 rows, d 1024), 13.3 instead of 13.0
+// (512 rows, d 4096).
 constexpr int kWideThreads = 1024;
 
 // One workgroup per output row; the row stays in registers between the sum
@@ -113,7 +119,6 @@ __global__ __launch_bounds__(kWideThreads) void resid_rmsnorm_kernel(const float
                                                                 T* __restrict__ out) {
   constexpr int THREADS = kWideThreads;
   constexpr int CH = kNormChunks * kRowThreads / THREADS;   // 16-byte chunks per thread: d <= 8192
-  constexpr int LIF = 8;                                     // partial loads in flight per chunk
   __shared__ float red[THREADS / kWave];
   const int r = blockIdx.x;
   const int sr = pos ? (r / n_pos) * seq + min(max(pos[r % n_pos], 0), seq - 1) : r;
@@ -128,14 +133,19 @@ __global__ __launch_bounds__(kWideThreads) void resid_rmsnorm_kernel(const float
     if (c < d) {
       v[j] = *reinterpret_cast<const f32x4*>(xr + c);
       int p = 0;
-      for (; p + LIF <= splits; p += LIF) {   // LIF loads in flight, added in order
-        f32x4 a[LIF];
+      auto group = [&](auto n) {   // n parts, every load before the first sum, added in order
+        constexpr int N = decltype(n)::value;
+        f32x4 a[N];
 #pragma unroll
-        for (int q = 0; q < LIF; ++q) a[q] = pr(p + q, c);
+        for (int q = 0; q < N; ++q) a[q] = pr(p + q, c);
 #pragma unroll
-        for (int q = 0; q < LIF; ++q) v[j] += a[q];
-      }
-      for (; p < splits; ++p) v[j] += pr(p, c);
+        for (int q = 0; q < N; ++q) v[j] += a[q];
+        p += N;
+      };
+      while (p + 8 <= splits) group(std::integral_constant<int, 8>{});
+      if (p + 4 <= splits) group(std::integral_constant<int, 4>{});
+      if (p + 2 <= splits) group(std::integral_constant<int, 2>{});
+      if (p < splits) v[j] += pr(p, c);
       if (!pos) *reinterpret_cast<f32x4*>(xr + c) = v[j];
     }
     ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
