@@ -20,8 +20,15 @@ struct dllm_model {
   const void* emb;
   const void* lm_head;
   // Largest split-K and LM-head workspace of a forward of at most 64 (i + 1)
-  // rows: smaller launches can take more parts and need more than larger ones
-  std::vector<size_t> part_max, lm_max;
+  // rows, filled as far as a query has needed it: smaller launches can take
+  // more parts and need more than larger ones
+  struct UpTo {
+    static constexpr int kKept = 1024;
+    size_t bytes[kKept];
+    int n = 0;
+  };
+  mutable UpTo part_max, lm_max;
+  mutable std::mutex upto_mu;
   std::vector<const void*> wqkv, wo, wgu, wdown;
   float2* rope;
   // kernel timing (dllm_profile_begin / end)
@@ -126,22 +133,30 @@ GemmSplits plan_gemms(const dllm_model_desc& d, int M) { return plan_gemms(d, M,
 // parts that only get dearer with the rows (their traffic), so the first of
 // them has the most parts.
 constexpr int kEnvRows = 64;
-constexpr int kEnvKept = 1024;   // entries kept with the model (65536 rows)
 constexpr int kMaxRows = 1 << 24;   // of one forward
-size_t part_bytes_of(const dllm_model_desc& d, int i) {
-  return plan_gemms(d, kEnvRows * i + 1, kEnvRows * (i + 1)).bytes;
+// the largest of bytes_of(0) .. bytes_of(n - 1), n >= 1; the first kKept running maxima stay with the model
+template <class F>
+size_t max_upto(const dllm_model* m, dllm_model::UpTo& u, int n, F bytes_of) {
+  const int kept = std::min(n, dllm_model::UpTo::kKept);
+  size_t b;
+  {
+    std::lock_guard<std::mutex> lock(m->upto_mu);
+    for (; u.n < kept; ++u.n) u.bytes[u.n] = std::max(u.n ? u.bytes[u.n - 1] : 0, bytes_of(u.n));
+    b = u.bytes[kept - 1];
+  }
+  for (int i = kept; i < n; ++i) b = std::max(b, bytes_of(i));
+  return b;
 }
 // largest split-K workspace of a forward of at most M rows
 size_t part_bytes_upto(const dllm_model* m, int M) {
-  const int n = (M + kEnvRows - 1) / kEnvRows;
-  size_t b = m->part_max[std::min(n, kEnvKept) - 1];
-  for (int i = kEnvKept; i < n; ++i) b = std::max(b, part_bytes_of(m->desc, i));
-  return b;
+  return max_upto(m, m->part_max, (M + kEnvRows - 1) / kEnvRows,
+                  [&](int i) { return plan_gemms(m->desc, kEnvRows * i + 1, kEnvRows * (i + 1)).bytes; });
 }
 // and of its LM head over at most R rows (past the kept ones it grows with R)
 size_t lm_bytes_upto(const dllm_model* m, int R) {
-  const int n = (R + kEnvRows - 1) / kEnvRows;
-  return std::max(m->lm_max[std::min(n, kEnvKept) - 1], lmhead_workspace(m->desc.dtype, R, m->desc.vocab));
+  auto own = [&](int r) { return lmhead_workspace(m->desc.dtype, r, m->desc.vocab); };
+  const int n = std::min((R + kEnvRows - 1) / kEnvRows, dllm_model::UpTo::kKept);
+  return std::max(max_upto(m, m->lm_max, n, [&](int i) { return own(kEnvRows * (i + 1)); }), own(R));
 }
 
 // packed lookahead layout of one forward (see dllm_forward_packed)
@@ -261,10 +276,6 @@ dllm_status dllm_model_create(const dllm_model_desc* desc, const dllm_weights* w
   m->wgu.assign(w->wgu, w->wgu + d.n_layers);
   m->wdown.assign(w->wdown, w->wdown + d.n_layers);
   m->rope = rope;
-  for (int i = 0; i < kEnvKept; ++i) {
-    m->part_max.push_back(std::max(i ? m->part_max[i - 1] : 0, part_bytes_of(d, i)));
-    m->lm_max.push_back(std::max(i ? m->lm_max[i - 1] : 0, lmhead_workspace(d.dtype, kEnvRows * (i + 1), d.vocab)));
-  }
   *out = m;
   return DLLM_OK;
 }
