@@ -540,7 +540,7 @@ struct DirectCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, kThreads = WM_ * WN_ * 64, kMinBlocks = MIN_BLOCKS;
   using TM = TileMma<T_, BM_, BN_, WM_, WN_, true, EARLY, FOLD>;
 };
-// fp32 tile: 64 x 64, 4 waves of 16 x 64, four workgroups to a CU.  The fp32
+// fp32 tile: 64 x 64, 4 waves of 16 x 64, up to five workgroups to a CU.  The fp32
 // matrix instructions run at a sixteenth of the bf16 rate, so a projection is
 // bound by them as soon as every SIMD has a wave, and by idle SIMDs before
 // that: this tile is small enough that a few hundred rows spread over all CUs,

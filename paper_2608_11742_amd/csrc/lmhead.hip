@@ -30,8 +30,8 @@ constexpr int kK = DLLM_TOPK_REG;
 // 4-6% slower at 512 and 4096 rows: every slice pays its first tile, where
 // the empty top-16 lists make many logits candidates, and the merge folds
 // twice the partials.
-// The small tile's workgroups hold 54 KB of LDS each, two run on a CU, and one
-// streams its weights while the other scans.
+// The small tile's workgroups hold 48 KB of LDS and 172 registers a thread, so
+// two run on a CU, and one streams its weights while the other scans.
 constexpr int kTargetWg = 256, kTargetWgSmall = 512;
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
