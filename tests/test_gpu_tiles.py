@@ -264,6 +264,28 @@ def test_forward_bf16_small_models(P, d, hd, F, S):
     model.close()
 
 
+# QKV of 64-wide heads in the tiles that the widths above do not reach: 256 x 192
+# parts, and 256 x 256 with V^T staged (sequences of whole 64-row tiles) and not
+@pytest.mark.parametrize("B_,S", [(1, 130), (6, 427), (41, 64)])
+def test_qkv_of_64_wide_heads(P, B_, S):
+    shape = ModelShape(n_layers=1, d_model=1536, n_heads=24, head_dim=64, d_ffn=256, vocab=600)
+    w_np = synth.model_weights_np(shape, seed=8, dtype="bf16")
+    model = P.Model(shape, {k: torch.from_numpy(v).to(DEV).bfloat16() for k, v in w_np.items()}, dtype="bf16",
+                    max_pos=512)
+    toks = synth.tokens_np(10, "toks", B_ * S, shape.vocab - 1).reshape(B_, S)
+    toks[:, S // 2:] = shape.mask_id
+    lm_pos = np.unique(np.array([0, S // 3, S // 2, S - 1], dtype=np.int32))
+    out = model.forward(torch.from_numpy(toks).to(DEV), torch.from_numpy(lm_pos).to(DEV), scale=2.0)
+    torch.cuda.synchronize()
+    got, n = out.numpy(), len(lm_pos)
+    for b in {0, B_ - 1}:
+        ref = softmax_stats(om.forward_logits(toks[b:b + 1], w_np, shape, lm_pos, scale=2.0, mirror=True).reshape(
+            -1, shape.vocab), 16)
+        print(compare_stats({k: v[b * n:(b + 1) * n] for k, v in got.items()}, ref, 2e-2, max_exceptions=2,
+                            id_ranks=4, label=f"bf16 hd 64 {B_} x {S} seq {b}"))
+    model.close()
+
+
 # packed attention: 64 heads x 512 rows is the first size whose 128-query
 # workgroups fill the CUs, 64 x 384 takes 32-query ones; blocks smaller than a
 # workgroup's queries, and shared rows that end inside one
