@@ -33,9 +33,9 @@ def lm_head():
 @pytest.mark.parametrize("R", [1, 16, 31, 32, 128, 129, 4000, 4096])
 def test_lm_head_stats_full_shape(P, lm_head, R):
     """vocab_entropy_topk with the 8B LM head (d 4096, V 126464).  Up to 129
-    rows (one or two 128-row tiles over all vocabulary slices, the multi-wave
-    merge of a decode's block forwards) every row is compared; at the step's
-    4096 (and a ragged 4000) rows, 24 sampled rows."""
+    rows (a 64-, 128- or 256-row tile over 256 or 512 vocabulary slices, the
+    merges of 4 and 8 waves) every row is compared; at the step's 4096 (and a
+    ragged 4000) rows, 24 sampled rows."""
     h = synth.weight_torch(21, "hidden", (R, B8.d_model), std=1.0, dtype="bf16", device=DEV)
     rs = torch.from_numpy((0.5 + 3 * synth.uniform01_np(22, "rs", R)).astype(np.float32)).to(DEV)
     out = P.Stats(R, 16, device=DEV)
@@ -235,7 +235,7 @@ def test_cached_step_two_layer_8b_width(P, b8_two_layer):
                          max_exceptions=max(2, 2 * own), id_ranks=4)
     print(rep1)
     # the same block in a ragged batch of 10 (320 rows per projection: QKV
-    # split-K parts on 256 x 192 tiles with a partial second row tile, O in 4
+    # split-K parts on 256 x 192 tiles with a partial second row tile, O in 2
     # and down in 8 K parts, gate/up on 256 x 192 tiles)
     out10 = model_p.forward(torch.from_numpy(blocks[:10]).to(DEV), torch.from_numpy(lm).to(DEV), pos_offset=Pn,
                             kv_prefix=kv, scale=1.0)

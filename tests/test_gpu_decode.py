@@ -125,7 +125,7 @@ def test_prefix_cached_baseline_matches_oracle(tiny, rule, k, tau, seed):
 
 # 2 layers of a 512 residual with the 8B workloads' vocabulary (126464): every
 # later forward of a block puts at most 32 rows per sequence through the LM
-# head, i.e. the 128-row tiles, the full set of vocabulary slices and the
+# head, i.e. the 64-row tiles, the full set of vocabulary slices and the
 # multi-wave merge of the 8B decode
 DECODE_BF16 = synth.ModelShape(n_layers=2, d_model=512, n_heads=4, head_dim=128, d_ffn=1536, vocab=126464)
 

@@ -120,8 +120,8 @@ def test_forward_small_bf16_against_mirror(P, small_bf16):
 
 
 def test_forward_tiny_f32_many_sequences(P, tiny):
-    """64 sequences of 200 tokens: the attention's pipelined schedule (256-query
-    tiles, three-slot key ring, ragged last tile); three sequences against the oracle."""
+    """64 sequences of 200 tokens: the attention's 128-query workgroups (the second
+    of a sequence partly filled, a ragged last key tile); three sequences against the oracle."""
     shape, w_np, model = tiny
     B_, S = 64, 200
     toks = synth.tokens_np(31, "toks", B_ * S, shape.vocab - 1).reshape(B_, S)
@@ -138,7 +138,7 @@ def test_forward_tiny_f32_many_sequences(P, tiny):
 
 
 def test_cached_prefix_many_blocks_tiny(P, tiny):
-    """A 40-position cached prefix shared by 64 blocks of 200 (pipelined
+    """A 40-position cached prefix shared by 64 blocks of 200 (128-query
     attention with prefix tiles); two blocks against the oracle."""
     from paper_2608_11742_amd._abi import KvCache
     shape, w_np, model = tiny

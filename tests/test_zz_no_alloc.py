@@ -21,8 +21,8 @@ def _case(R, d, V, seed):
 
 def test_noalloc_matches_the_workspace_entry_point_on_consecutive_calls():
     import paper_2608_11742_amd as P
-    # the 8B vocabulary at 300 rows (two 256-row tiles), then fewer rows and a
-    # smaller ragged vocabulary (one 128-row tile, more partials per row):
+    # the 8B vocabulary at 300 rows, then fewer rows and a smaller ragged
+    # vocabulary (a 64-row tile, more partials per row):
     # the second call must not see the first call's partials
     for R, d, V, seed in [(300, 512, 126464, 60), (37, 256, 30011, 63)]:
         h, w, rs = _case(R, d, V, seed)
